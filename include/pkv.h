@@ -299,13 +299,13 @@ size_t pkv_prefill_workspace_bytes(int32_t num_seqs, int32_t total_new, int32_t 
  * all previously computed K/V). Sequence i's single query q[i] attends over all
  * seq_lens[i] keys (the cached context plus the token this step appended):
  *   out[i][h] = sum_{t < seq_lens[i]} softmax_t(scale * <q[i][h], K[t]>) V[t].
- * The key range is cut into splits whose boundaries depend only on key positions; each split
- * writes a partial result to the workspace and a second kernel merges them with their
- * log-sum-exp weights. q, out: bf16 [num_seqs][num_q_heads][head_dim]; lse: float
+ * A batch too small to fill the chip has its key ranges cut into splits; each split writes a
+ * partial result to the workspace and a second kernel merges them with their log-sum-exp
+ * weights. The cuts depend on the call's sizes and each sequence's length only. q, out: bf16 [num_seqs][num_q_heads][head_dim]; lse: float
  * [num_seqs][num_q_heads] or NULL; seq_lens: int32 [num_seqs], each >= 1. max_seq_len (host)
  * >= every seq_lens[i]. workspace: device memory of at least pkv_decode_workspace_bytes
- * (non-zero whenever num_seqs > 0: it also holds the order in which sequences are
- * scheduled, longest first), 16-byte aligned, owned by the caller, not read back; calls
+ * (non-zero whenever num_seqs > 0: it also holds the order in which the sequences of a long
+ * batch are scheduled, longest first), 16-byte aligned, owned by the caller, not read back; calls
  * that share a workspace must not overlap. */
 pkv_status pkv_decode_attention(const pkv_paged_kv* kv, const void* q, int32_t num_q_heads,
                                 const int32_t* block_tables, int32_t max_blocks,
@@ -349,7 +349,7 @@ pkv_status pkv_copy_blocks(const pkv_paged_kv* kv, const int32_t* pairs, int32_t
  * (zero sequences or zero new tokens). Both read the same pool, so the new tokens of both
  * batches must have been appended before the call. One fused kernel runs prefill workgroups
  * (matrix-core bound) and decode workgroups (HBM bound) side by side on every compute unit,
- * between the decode's ordering and merge kernels. The two batches' outputs must not
+ * between the decode's ordering and merge kernels (where it has them). The two batches' outputs must not
  * overlap. Errors are those of the two calls. */
 pkv_status pkv_mixed_attention(const pkv_paged_kv* kv, int32_t num_q_heads, float scale,
                                const void* q, const int32_t* block_tables, int32_t max_blocks,

@@ -1,62 +1,95 @@
-// Paged decode attention for gfx950: the decode launch (an ordering kernel, the split work
-// items, and the merge of split partial results). The work-item body is in decode_impl.h.
+// Paged decode attention for gfx950: the decode launch (an ordering kernel for long batches, the
+// work items, and the merge of split partial results where sequences split). The work-item
+// bodies are in decode_impl.h.
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "decode_impl.h"
-#include "launch.h"
+#include "decode_plan.h"
 
 namespace pkv {
 namespace {
 
 constexpr int kWaves = 4;  // waves per workgroup of the merge kernel
 
-// Work item = (sequence, kv head, split) = one single-wave workgroup, so a compute unit takes
-// new work as soon as any wave ends (work items differ in length).
+// One wave per work item: a compute unit takes new work as soon as any wave ends (work items
+// differ in length).
 template <int D>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_partial_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache,
     const uint16_t* __restrict__ v_cache, const int32_t* __restrict__ block_tables,
-    int32_t max_blocks, const int32_t* __restrict__ seq_lens, int32_t num_seqs, int32_t hq,
-    int32_t hkv, int32_t num_blocks, int32_t split_keys, int32_t max_splits, float scale_log2,
-    float* __restrict__ ws_o, float* __restrict__ ws_ml, uint16_t* __restrict__ out,
-    float* __restrict__ lse, const int32_t* __restrict__ order) {
-  dec::decode_body<D>(q, k_cache, v_cache, block_tables, max_blocks, seq_lens, num_seqs, hq, hkv,
-                      num_blocks, split_keys, max_splits, scale_log2, ws_o, ws_ml, out, lse,
-                      order, blockIdx.x);
+    int32_t max_blocks, dec::DecodeWork work, int32_t hq, int32_t hkv, int32_t num_blocks,
+    float scale_log2, float* __restrict__ ws_o, float* __restrict__ ws_ml,
+    uint16_t* __restrict__ out, float* __restrict__ lse) {
+  dec::decode_body<D>(q, k_cache, v_cache, block_tables, max_blocks, work, hq, hkv, num_blocks,
+                      scale_log2, ws_o, ws_ml, out, lse, blockIdx.x);
+}
+
+// kParts waves per work item, merged inside the workgroup.
+template <int D, int kParts>
+__global__ __launch_bounds__(64 * kParts) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void decode_group_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache,
+    const uint16_t* __restrict__ v_cache, const int32_t* __restrict__ block_tables,
+    int32_t max_blocks, dec::DecodeWork work, int32_t hq, int32_t hkv, int32_t num_blocks,
+    float scale_log2, float* __restrict__ ws_o, float* __restrict__ ws_ml,
+    uint16_t* __restrict__ out, float* __restrict__ lse) {
+  __shared__ __align__(16) dec::DecodeSmem<D, kParts> sm;
+  dec::decode_group_body<D, kParts, kParts>(q, k_cache, v_cache, block_tables, max_blocks, work,
+                                            hq, hkv, num_blocks, scale_log2, ws_o, ws_ml, out,
+                                            lse, blockIdx.x, sm);
 }
 
 // One wave per (sequence, query head): combine the splits' partial (m_s, l_s, acc_s):
 //   out = sum_s 2^(m_s - M) acc_s / sum_s 2^(m_s - M) l_s,   M = max_s m_s.
+// Lane s of a round of 64 holds split s's maximum and weight sum, so a round waits for two
+// loads and not for two per split; the outputs' loads do not depend on one another.
 template <int D>
 __global__ __launch_bounds__(256) void decode_merge_kernel(
     const float* __restrict__ ws_o, const float* __restrict__ ws_ml,
     const int32_t* __restrict__ seq_lens, int32_t num_seqs, int32_t hq, int32_t split_keys,
-    int32_t max_splits, uint16_t* __restrict__ out, float* __restrict__ lse) {
+    int32_t max_splits, int32_t max_keys, uint16_t* __restrict__ out, float* __restrict__ lse) {
   constexpr int PER = D / 64;  // dims per lane
   const int64_t item = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (item >= (int64_t)num_seqs * hq) return;
   const int i = (int)(item / hq);
-  // the partial kernel's cut of an over-long length (at most max_splits splits)
-  const int len = min(seq_lens[i], max_splits * split_keys);
+  const int len = min(seq_lens[i], max_keys);
   const int nsplit = (len + split_keys - 1) / split_keys;
   if (nsplit <= 1) return;  // written directly by the partial kernel
   const size_t base = (size_t)item * max_splits;
   float mmax = -INFINITY;
-  for (int s = 0; s < nsplit; ++s) mmax = fmaxf(mmax, ws_ml[(base + s) * 2]);
+  for (int s = lane; s < nsplit; s += 64) mmax = fmaxf(mmax, ws_ml[(base + s) * 2]);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) mmax = fmaxf(mmax, __shfl_xor(mmax, o));
+  const float m_sub = dec::finite_max(mmax);
   float den = 0.f;
   float o[PER];
 #pragma unroll
   for (int e = 0; e < PER; ++e) o[e] = 0.f;
-  for (int s = 0; s < nsplit; ++s) {
-    const float w = fast_exp2(ws_ml[(base + s) * 2] - mmax);
-    den += w * ws_ml[(base + s) * 2 + 1];
-    const float* src = ws_o + (base + s) * D + lane * PER;
+  for (int s0 = 0; s0 < nsplit; s0 += 64) {
+    const int n = min(nsplit - s0, 64);
+    float w = 0.f;
+    if (lane < n) {
+      w = fast_exp2(ws_ml[(base + s0 + lane) * 2] - m_sub);
+      den += w * ws_ml[(base + s0 + lane) * 2 + 1];
+    }
+    const float* src = ws_o + (base + s0) * D + lane * PER;
+    // eight splits' loads at a time (past the last one: its own again, with no weight)
+    for (int s = 0; s < n; s += 8) {
 #pragma unroll
-    for (int e = 0; e < PER; ++e) o[e] += w * src[e];
+      for (int k = 0; k < 8; ++k) {
+        const float ws = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), s + k));
+        const float* from = src + (size_t)min(s + k, n - 1) * D;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) o[e] += ws * from[e];
+      }
+    }
   }
+#pragma unroll
+  for (int k = 32; k >= 1; k >>= 1) den += __shfl_xor(den, k);
   const float inv = 1.f / den;
   uint16_t* dst = out + (size_t)item * D + lane * PER;
   if constexpr (PER == 2) {
@@ -124,6 +157,13 @@ __global__ __launch_bounds__(kOrderThreads) void decode_order_kernel(
 }
 
 
+// Waves of the decode kernels that the chip holds at once (two on each of 256 x 4 SIMDs).
+constexpr int64_t kWaveSlots = 2048;
+// Work items past which a launch stays at one wave each (a grid holds 2^32 threads).
+constexpr int64_t kMaxWideItems = int64_t(1) << 20;
+// KV bytes (at the host's longest length) from which a decode is ordered longest first.
+constexpr int64_t kOrderBytes = int64_t(512) << 20;
+
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
@@ -153,11 +193,9 @@ hipError_t decode_scratch(void** ptr) {
 }
 
 int32_t decode_split_keys(int32_t num_seqs, int32_t hkv, int32_t max_seq_len) {
-  // Longest split first (every split pays a prologue of dependent table and first KV loads
-  // plus a partial write, so fewer, longer splits stream better); shorten it while the grid
-  // would hold too few waves to keep all 256 compute units streaming (aim for >= 8 waves
-  // per unit). A function of the call's sizes only, so a given call always splits
-  // identically.
+  // The finest cut a call may be planned with, which its workspace is sized for: 4096 keys,
+  // halved while a grid of one-wave items would hold fewer than 2048 waves. A function of the
+  // call's sizes only, so a given call always needs the same workspace.
   int32_t split = 4096;
   while (split > 64) {
     const int64_t waves =
@@ -181,8 +219,47 @@ size_t decode_workspace_bytes(int32_t num_seqs, int32_t hq, int32_t hkv, int32_t
 DecodePlan decode_plan(const KvView& kv, int32_t hq, int32_t num_seqs, int32_t max_seq_len,
                        void* workspace) {
   DecodePlan p;
-  p.split = decode_split_keys(num_seqs, kv.hkv, max_seq_len);
-  p.max_splits = (max_seq_len + p.split - 1) / p.split;
+  // What the workspace holds, and where over-long lengths are cut: the plan below never makes
+  // more splits than decode_split_keys does.
+  const int32_t base_split = decode_split_keys(num_seqs, kv.hkv, max_seq_len);
+  p.max_keys = (max_seq_len + base_split - 1) / base_split * base_split;
+  // (sequence, kv head) pairs: the least number of work items
+  const int64_t groups = (int64_t)num_seqs * kv.hkv;
+  // Shares per item. Cutting an item between the waves of one workgroup costs one LDS merge
+  // and no launch, and evens out the waves' lengths, so four shares are the rule. Eight pay
+  // where four would leave wave slots empty and some sequences are long enough to run on
+  // alone (48 sequences of 256-4096 keys, 64/8 heads: 84 us against 104; at 512 pairs and up
+  // four are better: 64 sequences of 200-1000 keys 28 us against 31). One wave per item is
+  // left where the pairs alone fill the chip and a share would be a step or two (512 sequences
+  // of at most 128 keys: 38 us against 48; the two meet at 600 keys).
+  int64_t target;  // waves aimed at
+  if ((groups >= kWaveSlots && max_seq_len <= 512) || groups >= kMaxWideItems) {
+    p.parts = 1;
+    target = 1;
+  } else if (groups < kWaveSlots / 4 && max_seq_len >= 2048) {
+    p.parts = 8;
+    target = kWaveSlots;
+  } else {
+    p.parts = 4;
+    target = kWaveSlots / 2;
+  }
+  // Splits across workgroups cost partial results and a merge launch (about 4 us), so they are
+  // made only while the items leave the chip without enough loads in flight, and of at least
+  // 1024 keys (4 sequences of 24-32k keys, 32/8 heads: 87 us, at 1.6 times fewer or 2 times
+  // more splits 92-104; one sequence of 800 keys: unsplit 11.3 us with its append, two
+  // splits 12.4). At most 16384 keys, so that one long sequence does not outlast the rest.
+  const int64_t want = std::max<int64_t>(1, target / (groups * p.parts));
+  int64_t split = std::max<int64_t>((p.max_keys + want - 1) / want, 1024);
+  split = std::max<int64_t>(std::min<int64_t>(split, 16384), base_split);
+  const int64_t unit = 32 * p.parts;
+  p.split = (int32_t)((split + unit - 1) / unit * unit);
+  p.max_splits = (p.max_keys + p.split - 1) / p.split;
+  p.items = groups * p.max_splits;
+  // Longest first pays where not every wave is resident at once and the batch is long against
+  // the ordering launch (4.5 us): 256 sequences of 256-4096 keys 383 us against 399, 256 of
+  // 400-1200 154 against 156, but 200 of 50-300 30 against 27.
+  p.ordered = p.items * p.parts > kWaveSlots &&
+              groups * max_seq_len * kv.head_dim * 4 >= (int64_t)kOrderBytes;
   p.order = static_cast<int32_t*>(workspace);
   p.ws_o = nullptr;
   p.ws_ml = nullptr;
@@ -190,7 +267,6 @@ DecodePlan decode_plan(const KvView& kv, int32_t hq, int32_t num_seqs, int32_t m
     p.ws_o = reinterpret_cast<float*>(static_cast<char*>(workspace) + order_bytes(num_seqs));
     p.ws_ml = p.ws_o + (size_t)num_seqs * hq * p.max_splits * kv.head_dim;
   }
-  p.items = (int64_t)num_seqs * kv.hkv * p.max_splits;
   return p;
 }
 
@@ -205,9 +281,10 @@ hipError_t launch_seq_order(const int32_t* lens, const int32_t* cu, int32_t num_
   return hipGetLastError();
 }
 
-hipError_t launch_decode_order(const int32_t* seq_lens, int32_t num_seqs, int32_t* order,
+hipError_t launch_decode_order(const DecodePlan& p, const int32_t* seq_lens, int32_t num_seqs,
                                hipStream_t stream) {
-  return launch_seq_order(seq_lens, nullptr, num_seqs, order, stream);
+  if (!p.ordered) return hipSuccess;
+  return launch_seq_order(seq_lens, nullptr, num_seqs, p.order, stream);
 }
 
 hipError_t launch_decode_merge(const KvView& kv, const DecodePlan& p, int32_t hq,
@@ -218,10 +295,10 @@ hipError_t launch_decode_merge(const KvView& kv, const DecodePlan& p, int32_t hq
   const dim3 mgrid((unsigned)((rows + kWaves - 1) / kWaves));
   if (kv.head_dim == 128)
     hipLaunchKernelGGL(decode_merge_kernel<128>, mgrid, dim3(256), 0, stream, p.ws_o, p.ws_ml,
-                       seq_lens, num_seqs, hq, p.split, p.max_splits, out, lse);
+                       seq_lens, num_seqs, hq, p.split, p.max_splits, p.max_keys, out, lse);
   else
     hipLaunchKernelGGL(decode_merge_kernel<64>, mgrid, dim3(256), 0, stream, p.ws_o, p.ws_ml,
-                       seq_lens, num_seqs, hq, p.split, p.max_splits, out, lse);
+                       seq_lens, num_seqs, hq, p.split, p.max_splits, p.max_keys, out, lse);
   return hipGetLastError();
 }
 
@@ -231,20 +308,18 @@ hipError_t launch_decode(const KvView& kv, const uint16_t* q, int32_t hq,
                          float scale, uint16_t* out, float* lse, void* workspace,
                          hipStream_t stream) {
   const DecodePlan p = decode_plan(kv, hq, num_seqs, max_seq_len, workspace);
+  if (p.items > INT32_MAX) return hipErrorInvalidValue;
   const dim3 grid((unsigned)p.items);
   const float scale_log2 = scale * kLog2e;
-  hipError_t err = launch_decode_order(seq_lens, num_seqs, p.order, stream);
+  hipError_t err = launch_decode_order(p, seq_lens, num_seqs, stream);
   if (err != hipSuccess) return err;
-  if (kv.head_dim == 128)
-    hipLaunchKernelGGL(decode_partial_kernel<128>, grid, dim3(64), 0, stream, q, kv.k, kv.v,
-                       block_tables, max_blocks, seq_lens, num_seqs, hq, kv.hkv,
-                       kv.num_blocks, p.split, p.max_splits, scale_log2, p.ws_o, p.ws_ml, out,
-                       lse, p.order);
-  else
-    hipLaunchKernelGGL(decode_partial_kernel<64>, grid, dim3(64), 0, stream, q, kv.k, kv.v,
-                       block_tables, max_blocks, seq_lens, num_seqs, hq, kv.hkv,
-                       kv.num_blocks, p.split, p.max_splits, scale_log2, p.ws_o, p.ws_ml, out,
-                       lse, p.order);
+  const bool wide = kv.head_dim == 128;
+  auto* kern = p.parts == 1 ? (wide ? decode_partial_kernel<128> : decode_partial_kernel<64>)
+             : p.parts == 4 ? (wide ? decode_group_kernel<128, 4> : decode_group_kernel<64, 4>)
+                            : (wide ? decode_group_kernel<128, 8> : decode_group_kernel<64, 8>);
+  hipLaunchKernelGGL(kern, grid, dim3(64 * p.parts), 0, stream, q, kv.k, kv.v, block_tables,
+                     max_blocks, decode_work(p, seq_lens, num_seqs), hq, kv.hkv, kv.num_blocks,
+                     scale_log2, p.ws_o, p.ws_ml, out, lse);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   return launch_decode_merge(kv, p, hq, seq_lens, num_seqs, out, lse, stream);

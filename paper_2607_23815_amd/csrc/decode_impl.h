@@ -3,11 +3,17 @@
 // context, split along the key axis ("split-K") so that every compute unit streams KV at the
 // HBM rate, followed by a merge of the splits' partial results by their log-sum-exp weights.
 //
-// Work item = (sequence, kv head, split) = one single-wave workgroup, so a compute unit
-// takes new work as soon as any wave ends (work items differ in length); there are no
-// barriers and no LDS. Sequences are taken longest first (a small ordering kernel runs
-// before the launch), so the launch does not end on a few long waves. Each wave streams its split
-// 32 keys (two 16-token blocks) at a time straight from HBM into the matrix-core operands:
+// Work item = (sequence, kv head, split). Its keys are shared out among the waves of one
+// workgroup (or one wave takes them all: see decode_plan for when), each wave streams its
+// share on its own, without barriers, and the shares' results meet in LDS once at the end. Cutting
+// inside the workgroup needs no partial results in memory and no merge launch, so splits
+// across workgroups are left to batches too small to fill the chip without them. HBM
+// bandwidth bounds a large batch (512 sequences of 512-2048 keys: 5.9 TB/s), the chain of
+// dependent loads (length, table, first K/V) and the launches a small one (one sequence of
+// 800 keys with its append: 15.8 us as ordering + 64-key splits + merge launches, 11.3 us as
+// one). A long batch is taken longest first (a small ordering kernel runs before the launch).
+// A wave streams 32 keys (two 16-token blocks) at a time straight from HBM into the
+// matrix-core operands:
 //   scores  S^T[32 keys][16 cols] = K[keys][D] . Q^T[D][cols]      (v_mfma 16x16x32 bf16)
 //   values  O^T[D][16 cols]      += V^T[D][32 keys] . P^T[keys][cols]
 // The columns are the g = Hq/Hkv query heads that share the kv head (g <= 16; unused columns
@@ -21,7 +27,7 @@
 // shuffles. Keys outside the sequence (tail slots of its last block, which may hold any bits,
 // NaN included) are removed by selection -- scores to -inf and V operands to zero -- never by
 // multiplying by a zero weight.
-// Split boundaries are multiples of the split size in key position only, so results are
+// The cuts depend on the call's sizes and each sequence's length only, so results are
 // bit-identical from run to run and independent of where blocks sit in the pool.
 #pragma once
 
@@ -43,6 +49,10 @@ __device__ __forceinline__ float wave_sum16(float x) {
   x += __shfl_xor(x, 32);
   return x;
 }
+
+// The maximum to subtract: a range whose scores are all -inf weighs nothing instead of
+// 2^(-inf + inf) = NaN, so that cutting a sequence's keys into more ranges brings in no NaN.
+__device__ __forceinline__ float finite_max(float m) { return m == -INFINITY ? 0.f : m; }
 
 // zero the 16-bit lanes of a 4-element V fragment whose key index (base + e) >= nvalid
 __device__ __forceinline__ u32x2 mask_v4(u32x2 v, int base, int nvalid) {
@@ -88,57 +98,32 @@ __device__ __forceinline__ void decode_load(DecodeFrag<D>& f, const uint16_t* __
   }
 }
 
-// The body of one decode work item (sequence rank, kv head, split), run by one wave.
+// One wave's share of a work item: the keys [k0, k1) of a sequence (k0 a multiple of 16), for
+// the columns of kv head kvh. Leaves the unnormalised output (lane (col, grp) holds dims
+// 16 db + 4 grp + 0..3 of column col), the running maximum (base 2) and the lane's part of the
+// weight sum. The range is not empty.
 template <int D>
-__device__ __forceinline__ void decode_body(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache,
-    const uint16_t* __restrict__ v_cache, const int32_t* __restrict__ block_tables,
-    int32_t max_blocks, const int32_t* __restrict__ seq_lens, int32_t num_seqs, int32_t hq,
-    int32_t hkv, int32_t num_blocks, int32_t split_keys, int32_t max_splits, float scale_log2,
-    float* __restrict__ ws_o, float* __restrict__ ws_ml, uint16_t* __restrict__ out,
-    float* __restrict__ lse, const int32_t* __restrict__ order, const int64_t item) {
+__device__ __forceinline__ void decode_range(
+    const bf16x8 (&qf)[D / 32], const uint16_t* __restrict__ k_cache,
+    const uint16_t* __restrict__ v_cache, const int32_t* __restrict__ table, int32_t max_blocks,
+    int32_t hkv, int32_t num_blocks, const int kvh, const int k0, const int k1,
+    const float scale_log2, f32x4 (&acc)[D / 16], float& m, float& lpart) {
   constexpr int KK = D / 32;   // k-steps of the score product
   constexpr int DB = D / 16;   // 16-dim blocks of the value product
   constexpr int SLAB = D * kBlockSize;
-  const int g = hq / hkv;
   const int lane = threadIdx.x & 63;
-  const int col = lane & 15;   // query head within the kv group (column)
-  const int grp = lane >> 4;   // lane group 0..3
-  const int64_t per_seq = (int64_t)hkv * max_splits;
-  const int rank = (int)(item / per_seq);
-  if (rank >= num_seqs) return;
-  const int i = order[rank];  // longest sequences first
-  const int rem = (int)(item % per_seq);
-  const int kvh = rem / max_splits;
-  const int sp = rem % max_splits;
-  // A length above the host's max_seq_len breaks the caller's contract; it is cut to the
-  // splits the launch planned (the merge cuts it the same way), and keys past the table are
-  // not attended, so such a call computes over fewer keys but never leaves its workspace.
-  // With max_seq_len <= max_blocks * 16 (checked on the host) every planned split starts
-  // inside the table, so no split is empty.
-  const int len = min(seq_lens[i], max_splits * split_keys);
-  const int nsplit = (len + split_keys - 1) / split_keys;  // 0 for a length < 1: no output
-  if (sp >= nsplit) return;
-  const int k0 = sp * split_keys;
-  int k1 = min(len, k0 + split_keys);
-  if ((k1 - 1) / kBlockSize >= max_blocks) k1 = max_blocks * kBlockSize;  // (no overflow)
-  const bool col_ok = col < g;
-  const int h = kvh * g + col;
-
-  bf16x8 qf[KK];
+  const int col = lane & 15;
+  const int grp = lane >> 4;
 #pragma unroll
-  for (int kk = 0; kk < KK; ++kk) {
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (col_ok) v = ld16(q + ((size_t)i * hq + h) * D + kk * 32 + grp * 8);
-    qf[kk] = as_bf16x8(v);
-  }
+  for (int db = 0; db < DB; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  m = -INFINITY;
+  lpart = 0.f;
 
-  // The split's blocks in per-lane register tables of 64 entries: chunk c holds, in lane l,
-  // the pool offset of the split's block 64 c + l, or of pool block 0 (a stand-in that is
-  // read but masked) for blocks past the split, past the table or out of the pool. Two
+  // The range's blocks in per-lane register tables of 64 entries: chunk c holds, in lane l,
+  // the pool offset of the range's block 64 c + l, or of pool block 0 (a stand-in that is
+  // read but masked) for blocks past the range, past the table or out of the pool. Two
   // chunks are live (the current one and the next), so every load below is unconditional
   // and a step's 24 loads issue back to back and overlap the previous step.
-  const int32_t* table = block_tables + (size_t)i * max_blocks;
   const int b_first = k0 / kBlockSize;
   const int nblk = (k1 - k0 + kBlockSize - 1) / kBlockSize;
   // (the load and the check are separate steps, so that the first two chunks' loads are both
@@ -161,12 +146,6 @@ __device__ __forceinline__ void decode_body(
                          : __builtin_amdgcn_readlane(tab_next, b - 64);
     return (size_t)e * hkv * SLAB + head_off;
   };
-
-  f32x4 acc[DB];
-#pragma unroll
-  for (int db = 0; db < DB; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY;
-  float lpart = 0.f;
 
   auto compute = [&](const DecodeFrag<D>& f, int t0) {
     const int nvalid = min(32, k1 - t0);
@@ -194,12 +173,13 @@ __device__ __forceinline__ void decode_body(
                      fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
     mx = wave_max16(mx);
     const float m_new = fmaxf(m, mx);
-    const float alpha = fast_exp2(m - m_new);
+    const float m_sub = finite_max(m_new);
+    const float alpha = fast_exp2(m - m_sub);
     float pv[8];
     float ps = 0.f;
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
-      pv[r] = fast_exp2(sv[r] - m_new);
+      pv[r] = fast_exp2(sv[r] - m_sub);
       ps += pv[r];
     }
     lpart = lpart * alpha + ps;
@@ -243,10 +223,85 @@ __device__ __forceinline__ void decode_body(
     compute(fb, t0 + 32);
     if (t0 + 64 >= k1) break;
   }
+}
 
+// The query operand of kv head kvh: lane (col, grp) holds dims 32 kk + 8 grp .. +7 of query
+// head kvh * g + col (zeros past the group's heads).
+template <int D>
+__device__ __forceinline__ void decode_load_q(const uint16_t* __restrict__ q, int i, int hq,
+                                              int g, int kvh, bf16x8 (&qf)[D / 32]) {
+  const int lane = threadIdx.x & 63;
+  const int col = lane & 15, grp = lane >> 4;
+#pragma unroll
+  for (int kk = 0; kk < D / 32; ++kk) {
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (col < g) v = ld16(q + ((size_t)i * hq + kvh * g + col) * D + kk * 32 + grp * 8);
+    qf[kk] = as_bf16x8(v);
+  }
+}
+
+// A decode launch's work list. Work item = (sequence rank, kv head, split); a sequence is cut
+// into splits of split_keys keys, and an item's keys into `parts` shares, one per wave
+// (parts = 1: one wave is the item). max_keys bounds every length (see decode_plan): a length
+// above it breaks the caller's contract and is cut to it (the merge cuts it the same way),
+// and keys past the table are not attended, so such a call computes over fewer keys but never
+// leaves its workspace. With max_seq_len <= max_blocks * 16 (checked on the host) every
+// split starts inside the table, so no split is empty.
+struct DecodeWork {
+  const int32_t* seq_lens;
+  const int32_t* order;  // sequences longest first, or null: in batch order
+  int32_t num_seqs;
+  int32_t split_keys, max_splits, max_keys;
+};
+struct DecodeItem {
+  int i, kvh, sp, nsplit, k0, k1;
+};
+// false: nothing to do (past the list, or past the sequence's splits; 0 splits for a length
+// below 1: no output)
+__device__ __forceinline__ bool decode_item(const DecodeWork& w, int32_t hkv, int32_t max_blocks,
+                                            int64_t item, DecodeItem& it) {
+  const int64_t per_seq = (int64_t)hkv * w.max_splits;
+  const int rank = (int)(item / per_seq);
+  if (rank >= w.num_seqs) return false;
+  it.i = w.order != nullptr ? w.order[rank] : rank;
+  const int rem = (int)(item % per_seq);
+  it.kvh = rem / w.max_splits;
+  it.sp = rem % w.max_splits;
+  const int len = min(w.seq_lens[it.i], w.max_keys);
+  it.nsplit = (len + w.split_keys - 1) / w.split_keys;
+  if (it.sp >= it.nsplit) return false;
+  it.k0 = it.sp * w.split_keys;
+  it.k1 = min(len, it.k0 + w.split_keys);
+  if ((it.k1 - 1) / kBlockSize >= max_blocks) it.k1 = max_blocks * kBlockSize;  // (no overflow)
+  return true;
+}
+
+// The body of a one-wave work item.
+template <int D>
+__device__ __forceinline__ void decode_body(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache,
+    const uint16_t* __restrict__ v_cache, const int32_t* __restrict__ block_tables,
+    int32_t max_blocks, const DecodeWork& work, int32_t hq, int32_t hkv, int32_t num_blocks,
+    float scale_log2, float* __restrict__ ws_o, float* __restrict__ ws_ml,
+    uint16_t* __restrict__ out, float* __restrict__ lse, const int64_t item) {
+  constexpr int DB = D / 16;
+  const int g = hq / hkv;
+  const int lane = threadIdx.x & 63;
+  const int col = lane & 15;   // query head within the kv group (column)
+  const int grp = lane >> 4;   // lane group 0..3
+  DecodeItem it;
+  if (!decode_item(work, hkv, max_blocks, item, it)) return;
+  const int i = it.i;
+  const int h = it.kvh * g + col;
+  bf16x8 qf[D / 32];
+  decode_load_q<D>(q, i, hq, g, it.kvh, qf);
+  f32x4 acc[DB];
+  float m, lpart;
+  decode_range<D>(qf, k_cache, v_cache, block_tables + (size_t)i * max_blocks, max_blocks, hkv,
+                  num_blocks, it.kvh, it.k0, it.k1, scale_log2, acc, m, lpart);
   const float l = wave_sum16(lpart);
-  if (!col_ok) return;
-  if (nsplit == 1) {
+  if (col >= g) return;
+  if (it.nsplit == 1) {
     const float inv = 1.f / l;
     uint16_t* o = out + ((size_t)i * hq + h) * D;
 #pragma unroll
@@ -258,7 +313,7 @@ __device__ __forceinline__ void decode_body(
     if (lse != nullptr && grp == 0) lse[(size_t)i * hq + h] = (m + log2f(l)) * kLn2;
     return;
   }
-  const size_t slot = ((size_t)i * hq + h) * max_splits + sp;
+  const size_t slot = ((size_t)i * hq + h) * work.max_splits + it.sp;
   float* o = ws_o + slot * D;
 #pragma unroll
   for (int db = 0; db < DB; ++db) {
@@ -268,6 +323,95 @@ __device__ __forceinline__ void decode_body(
   if (grp == 0) {
     ws_ml[slot * 2 + 0] = m;
     ws_ml[slot * 2 + 1] = l;
+  }
+}
+
+// Shares' results of one work item on their way to each other.
+template <int D, int kParts>
+struct DecodeSmem {
+  float o[kParts][16][D + 4];  // unnormalised output [share][column][dim] (padded rows)
+  float m[kParts][16], l[kParts][16];
+};
+
+// The body of a work item run by a workgroup of kWgWaves waves: its keys are cut into kParts
+// equal shares (of 32-key steps), wave w takes shares w, w + kWgWaves, ..., and the shares'
+// results meet in LDS, where they are merged by their log-sum-exp weights in share order. The
+// cut depends on the item's keys only, so the result does not depend on kWgWaves.
+template <int D, int kParts, int kWgWaves>
+__device__ __forceinline__ void decode_group_body(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache,
+    const uint16_t* __restrict__ v_cache, const int32_t* __restrict__ block_tables,
+    int32_t max_blocks, const DecodeWork& work, int32_t hq, int32_t hkv, int32_t num_blocks,
+    float scale_log2, float* __restrict__ ws_o, float* __restrict__ ws_ml,
+    uint16_t* __restrict__ out, float* __restrict__ lse, const int64_t item,
+    DecodeSmem<D, kParts>& sm) {
+  static_assert(kParts % kWgWaves == 0, "every wave takes the same number of shares");
+  constexpr int DB = D / 16;
+  const int g = hq / hkv;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  DecodeItem it;
+  if (!decode_item(work, hkv, max_blocks, item, it)) return;  // (workgroup-uniform)
+  const int share = ((it.k1 - it.k0 + kParts - 1) / kParts + 31) / 32 * 32;
+  bf16x8 qf[D / 32];
+  decode_load_q<D>(q, it.i, hq, g, it.kvh, qf);
+#pragma unroll 1
+  for (int part = wave; part < kParts; part += kWgWaves) {
+    f32x4 acc[DB];
+    float m, lpart;
+    const int col = lane & 15, grp = lane >> 4;
+    const int k0 = it.k0 + part * share;
+    if (k0 >= it.k1) {  // an empty share: no weight
+      if (lane < 16) sm.m[part][lane] = -INFINITY;
+      continue;
+    }
+    decode_range<D>(qf, k_cache, v_cache, block_tables + (size_t)it.i * max_blocks, max_blocks,
+                    hkv, num_blocks, it.kvh, k0, min(it.k1, k0 + share), scale_log2, acc, m,
+                    lpart);
+    const float l = wave_sum16(lpart);
+    if (col < g) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+        st16(&sm.o[part][col][db * 16 + 4 * grp], __builtin_bit_cast(u32x4, acc[db]));
+      if (grp == 0) {
+        sm.m[part][col] = m;
+        sm.l[part][col] = l;
+      }
+    }
+  }
+  __syncthreads();
+  // one thread per (column, 4 dims), over the shares that have keys
+  const int used = (it.k1 - it.k0 + share - 1) / share;
+  for (int u = threadIdx.x; u < g * (D / 4); u += 64 * kWgWaves) {
+    const int col = u / (D / 4), d = (u % (D / 4)) * 4;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int s = 0; s < kParts; ++s) mx = fmaxf(mx, sm.m[s][col]);
+    float den = 0.f;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < kParts; ++s) {
+      if (s >= used) break;
+      const float w = fast_exp2(sm.m[s][col] - finite_max(mx));
+      den += w * sm.l[s][col];
+      const f32x4 a = __builtin_bit_cast(f32x4, ld16(&sm.o[s][col][d]));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] += w * a[e];
+    }
+    const size_t row = (size_t)it.i * hq + it.kvh * g + col;
+    if (it.nsplit == 1) {
+      const float inv = 1.f / den;
+      st8(out + row * D + d, u32x2{pack_bf16x2(o[0] * inv, o[1] * inv),
+                                   pack_bf16x2(o[2] * inv, o[3] * inv)});
+      if (lse != nullptr && d == 0) lse[row] = (mx + log2f(den)) * kLn2;
+    } else {
+      const size_t slot = row * work.max_splits + it.sp;
+      st16(ws_o + slot * D + d, __builtin_bit_cast(u32x4, o));
+      if (d == 0) {
+        ws_ml[slot * 2 + 0] = mx;
+        ws_ml[slot * 2 + 1] = den;
+      }
+    }
   }
 }
 

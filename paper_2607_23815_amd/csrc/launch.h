@@ -54,7 +54,7 @@ hipError_t launch_prefill(const KvView& kv, const uint16_t* q, int32_t hq,
                           int32_t max_total_len, float scale, uint16_t* out, float* lse,
                           void* workspace, hipStream_t stream);
 
-// Decode: keys are cut into splits of `split_keys` (a multiple of 32) keys.
+// Decode: the shortest splits (a multiple of 32 keys) the workspace has room for.
 int32_t decode_split_keys(int32_t num_seqs, int32_t hkv, int32_t max_seq_len);
 size_t decode_workspace_bytes(int32_t num_seqs, int32_t hq, int32_t hkv, int32_t head_dim,
                               int32_t max_seq_len);
@@ -63,6 +63,9 @@ size_t decode_workspace_bytes(int32_t num_seqs, int32_t hq, int32_t hkv, int32_t
 // kernel, and the merge of partial results (nothing when no sequence splits).
 struct DecodePlan {
   int32_t split, max_splits;
+  int32_t parts;     // waves' shares per work item (1: one wave is the item)
+  int32_t max_keys;  // lengths are cut to it
+  bool ordered;      // the launch takes its sequences longest first
   int32_t* order;
   float* ws_o;
   float* ws_ml;
@@ -70,7 +73,8 @@ struct DecodePlan {
 };
 DecodePlan decode_plan(const KvView& kv, int32_t hq, int32_t num_seqs, int32_t max_seq_len,
                        void* workspace);
-hipError_t launch_decode_order(const int32_t* seq_lens, int32_t num_seqs, int32_t* order,
+// (nothing when the plan does not order)
+hipError_t launch_decode_order(const DecodePlan& p, const int32_t* seq_lens, int32_t num_seqs,
                                hipStream_t stream);
 // Longest-first order of sequences by lens[i] (+ cu[i + 1] - cu[i] when cu is given), and the
 // bytes it takes in a workspace (256-byte rounded).

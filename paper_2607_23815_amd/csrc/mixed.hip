@@ -9,16 +9,17 @@
 // has the same residue mod 8), so the (sequence, kv head) groups keep their XCD and L2. The
 // decode items follow the longest-first order of the decode launch, and the results are
 // bit-identical to a prefill launch followed by a decode launch.
-#include "decode_impl.h"
+#include "decode_plan.h"
 #include "launch.h"
 #include "prefill_impl.h"
 
 namespace pkv {
 namespace {
 
-constexpr int kDecodePerWg = pre::kThreads / 64;  // one decode item per wave
+constexpr int kDecodePerWg = pre::kThreads / 64;  // one-wave decode items per workgroup
 
-template <int D>
+// kParts: shares per decode item (1: four one-wave items per workgroup)
+template <int D, int kParts>
 __global__ __attribute__((amdgpu_flat_work_group_size(pre::kThreads, pre::kThreads),
                           amdgpu_waves_per_eu(2, 2)))
 void mixed_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache,
@@ -28,11 +29,13 @@ void mixed_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
                   int32_t hkv, int32_t num_blocks, int32_t qtiles, float scale_log2,
                   uint16_t* __restrict__ out, float* __restrict__ lse,
                   const uint16_t* __restrict__ dq, const int32_t* __restrict__ d_tables,
-                  int32_t d_max_blocks, const int32_t* __restrict__ seq_lens, int32_t d_num_seqs,
-                  int32_t split_keys, int32_t max_splits, float* __restrict__ ws_o,
+                  int32_t d_max_blocks, dec::DecodeWork work, float* __restrict__ ws_o,
                   float* __restrict__ ws_ml, uint16_t* __restrict__ d_out,
-                  float* __restrict__ d_lse, const int32_t* __restrict__ order, int32_t p8,
-                  int32_t d8, int64_t d_items) {
+                  float* __restrict__ d_lse, int32_t p8, int32_t d8, int64_t d_items) {
+  __shared__ __align__(16) union {
+    pre::PrefillSmem<D> prefill;
+    dec::DecodeSmem<D, kParts> decode;
+  } sm;
   const unsigned x = blockIdx.x & 7;
   const unsigned pos = blockIdx.x >> 3;
   const int64_t t8 = (int64_t)p8 + d8;
@@ -40,16 +43,23 @@ void mixed_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
   const int64_t before = (int64_t)pos * d8 / t8;
   const int64_t upto = ((int64_t)pos + 1) * d8 / t8;
   if (upto > before) {
-    const int64_t item =
-        ((int64_t)before * 8 + x) * kDecodePerWg + (int64_t)(threadIdx.x >> 6);
-    if (item >= d_items) return;
-    dec::decode_body<D>(dq, k_cache, v_cache, d_tables, d_max_blocks, seq_lens, d_num_seqs, hq,
-                        hkv, num_blocks, split_keys, max_splits, scale_log2, ws_o, ws_ml, d_out,
-                        d_lse, order, item);
+    const int64_t wg = (int64_t)before * 8 + x;
+    if constexpr (kParts == 1) {
+      const int64_t item =
+          wg * kDecodePerWg + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+      if (item >= d_items) return;
+      dec::decode_body<D>(dq, k_cache, v_cache, d_tables, d_max_blocks, work, hq, hkv,
+                          num_blocks, scale_log2, ws_o, ws_ml, d_out, d_lse, item);
+    } else {
+      if (wg >= d_items) return;
+      dec::decode_group_body<D, kParts, kDecodePerWg>(
+          dq, k_cache, v_cache, d_tables, d_max_blocks, work, hq, hkv, num_blocks, scale_log2,
+          ws_o, ws_ml, d_out, d_lse, wg, sm.decode);
+    }
   } else {
     pre::prefill_body<D>(q, k_cache, v_cache, block_tables, max_blocks, cached_lens,
                          cu_new_lens, num_seqs, hq, hkv, num_blocks, qtiles, scale_log2, out,
-                         lse, (unsigned)((pos - before) * 8 + x));
+                         lse, (unsigned)((pos - before) * 8 + x), sm.prefill);
   }
 }
 
@@ -64,28 +74,24 @@ hipError_t launch_mixed(const KvView& kv, int32_t hq, float scale, const uint16_
                         uint16_t* d_out, float* d_lse, void* workspace, hipStream_t stream) {
   const pre::PrefillGrid pg = pre::prefill_grid(hq, kv.hkv, num_seqs, max_new_len);
   const DecodePlan dp = decode_plan(kv, hq, d_num_seqs, max_seq_len, workspace);
-  const int64_t d_wgs = (dp.items + kDecodePerWg - 1) / kDecodePerWg;
+  const int64_t d_wgs =
+      dp.parts == 1 ? (dp.items + kDecodePerWg - 1) / kDecodePerWg : dp.items;
   const int64_t p8 = pg.items / 8;  // a multiple of 8 by construction
   const int64_t d8 = (d_wgs + 7) / 8;
   if (8 * (p8 + d8) > INT32_MAX) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(8 * (p8 + d8)));
   const float scale_log2 = scale * kLog2e;
-  hipError_t err = launch_decode_order(seq_lens, d_num_seqs, dp.order, stream);
+  hipError_t err = launch_decode_order(dp, seq_lens, d_num_seqs, stream);
   if (err != hipSuccess) return err;
-  if (kv.head_dim == 128)
-    hipLaunchKernelGGL(mixed_kernel<128>, grid, dim3(pre::kThreads), 0, stream, q, kv.k, kv.v,
-                       block_tables, max_blocks, cached_lens, cu_new_lens, num_seqs, hq, kv.hkv,
-                       kv.num_blocks, (int32_t)pg.qtiles, scale_log2, out, lse, dq,
-                       d_block_tables, d_max_blocks, seq_lens, d_num_seqs, dp.split,
-                       dp.max_splits, dp.ws_o, dp.ws_ml, d_out, d_lse, dp.order, (int32_t)p8,
-                       (int32_t)d8, dp.items);
-  else
-    hipLaunchKernelGGL(mixed_kernel<64>, grid, dim3(pre::kThreads), 0, stream, q, kv.k, kv.v,
-                       block_tables, max_blocks, cached_lens, cu_new_lens, num_seqs, hq, kv.hkv,
-                       kv.num_blocks, (int32_t)pg.qtiles, scale_log2, out, lse, dq,
-                       d_block_tables, d_max_blocks, seq_lens, d_num_seqs, dp.split,
-                       dp.max_splits, dp.ws_o, dp.ws_ml, d_out, d_lse, dp.order, (int32_t)p8,
-                       (int32_t)d8, dp.items);
+  const bool wide = kv.head_dim == 128;
+  auto* kern = dp.parts == 1 ? (wide ? mixed_kernel<128, 1> : mixed_kernel<64, 1>)
+             : dp.parts == 4 ? (wide ? mixed_kernel<128, 4> : mixed_kernel<64, 4>)
+                             : (wide ? mixed_kernel<128, 8> : mixed_kernel<64, 8>);
+  hipLaunchKernelGGL(kern, grid, dim3(pre::kThreads), 0, stream, q, kv.k, kv.v, block_tables,
+                     max_blocks, cached_lens, cu_new_lens, num_seqs, hq, kv.hkv, kv.num_blocks,
+                     (int32_t)pg.qtiles, scale_log2, out, lse, dq, d_block_tables, d_max_blocks,
+                     decode_work(dp, seq_lens, d_num_seqs), dp.ws_o, dp.ws_ml, d_out, d_lse,
+                     (int32_t)p8, (int32_t)d8, dp.items);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   return launch_decode_merge(kv, dp, hq, seq_lens, d_num_seqs, d_out, d_lse, stream);

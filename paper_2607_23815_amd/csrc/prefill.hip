@@ -23,14 +23,15 @@ void prefill_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     uint16_t* __restrict__ out, float* __restrict__ lse, int32_t split_keys,
                     int32_t nsplit, float* __restrict__ ws_o, float* __restrict__ ws_ml,
                     const int32_t* __restrict__ order) {
+  __shared__ __align__(16) pre::PrefillSmem<D> sm;
   if constexpr (kPlan)
     pre::prefill_body<D>(q, k_cache, v_cache, block_tables, max_blocks, cached_lens,
                          cu_new_lens, num_seqs, hq, hkv, num_blocks, qtiles, scale_log2, out,
-                         lse, blockIdx.x, split_keys, nsplit, ws_o, ws_ml, order);
+                         lse, blockIdx.x, sm, split_keys, nsplit, ws_o, ws_ml, order);
   else
     pre::prefill_body<D>(q, k_cache, v_cache, block_tables, max_blocks, cached_lens,
                          cu_new_lens, num_seqs, hq, hkv, num_blocks, qtiles, scale_log2, out,
-                         lse, blockIdx.x);
+                         lse, blockIdx.x, sm);
 }
 
 // Merge of the split partial results: one wave per (new token, query head) row of sequence

@@ -638,10 +638,9 @@ __device__ __forceinline__ void prefill_body(const uint16_t* __restrict__ q, con
                     const int32_t* __restrict__ cu_new_lens, int32_t num_seqs, int32_t hq,
                     int32_t hkv, int32_t num_blocks, int32_t qtiles, float scale_log2,
                     uint16_t* __restrict__ out, float* __restrict__ lse, const unsigned wg,
-                    int32_t split_keys = 0, int32_t nsplit = 1, float* __restrict__ ws_o = nullptr,
+                    PrefillSmem<D>& sm, int32_t split_keys = 0, int32_t nsplit = 1, float* __restrict__ ws_o = nullptr,
                     float* __restrict__ ws_ml = nullptr,
                     const int32_t* __restrict__ order = nullptr) {
-  __shared__ __align__(16) PrefillSmem<D> sm;
   // XCD-aware mapping: workgroup id b runs on XCD b % 8 (a mixed launch passes a `wg` with
   // the same residue mod 8 as its workgroup id). The unit that must stay on one XCD
   // is a (sequence, kv head) group -- its query tiles read the same K/V and share that XCD's

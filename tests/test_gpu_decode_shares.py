@@ -1,0 +1,59 @@
+"""GPU tier: the decode plan's cuts (an item's keys shared out among one, four or eight waves of
+a workgroup; splits across workgroups) at the sizes where they change, against the fp64 oracle,
+and the fused launch's decode half under the same plans, bit for bit."""
+import numpy as np
+import pytest
+
+import workloads as W
+from tests.gpu_util import dev_pools, say
+from tests.test_gpu_decode import check, oracle_decode, run_decode
+from tests.test_gpu_mixed import _run, _same
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # four shares, one split: shares of one step, of one key, empty last shares
+    ("shares4", 8, 2, 128, [0, 1, 31, 32, 33, 95, 96, 127, 128, 129, 1000, 1022, 1023]),
+    # four shares, splits of 1024 keys: a last split of one key, of one block
+    ("shares4_splits", 4, 1, 64, [1023, 1024, 1039, 1040, 2045]),
+    # eight shares, splits of 1024 keys (shares of 128), next to sequences of one split
+    ("shares8_splits", 32, 8, 128, [2047, 2048, 3071, 3072, 3073, 40, 1023, 1024]),
+    # more than 64 splits of one sequence: the merge takes them in rounds
+    ("splits_over_64", 4, 1, 64, [70001, 65, 66000]),
+    # 512 pairs and up: four shares, unsplit, longer than 2048 keys
+    ("shares4_many", 64, 64, 64, [2100, 5, 300, 2047, 2048, 17, 64, 129]),
+    # one wave per item: many pairs of at most 512 keys
+    ("one_wave", 64, 64, 64, [511, 510, 0, 1, 16, 31, 32, 33] + [7] * 24),
+    # the same pairs with one key more: four shares
+    ("one_wave_edge", 64, 64, 64, [512, 511, 0, 1, 16, 31, 32, 33] + [7] * 24),
+]
+
+
+def _case(c, prefill=False):
+    name, hq, hkv, d, ctx = c
+    batches = (W.BatchSpec("decode", len(ctx), W.Dist.const(1), W.Dist.const(1)),)
+    if prefill:
+        batches = (W.BatchSpec("prefill", 2, W.Dist.const(1), W.Dist.const(1)),) + batches
+    spec = W.WorkloadSpec(f"decode_{name}", 180 + CASES.index(c), hq, hkv, d, batches,
+                          ("scale", 1.25))
+    if prefill:
+        return W.make_case(spec, prefix_override=[[40, 300], ctx], new_override=[[70, 9], None])
+    return W.make_case(spec, prefix_override=[ctx])
+
+
+@pytest.mark.parametrize("c", CASES, ids=lambda c: c[0])
+def test_decode_shares_match_oracle(gpu_lib, c):
+    say(f"[decode shares] {c[0]}")
+    case = _case(c)
+    check(c[0], run_decode(gpu_lib, case), oracle_decode(case))
+
+
+@pytest.mark.parametrize("c", CASES, ids=lambda c: c[0])
+def test_mixed_decode_shares_equal_the_decode_call(gpu_lib, c):
+    say(f"[mixed shares] {c[0]}")
+    case = _case(c, prefill=True)
+    pk, pv = dev_pools(case)
+    sep = _run(gpu_lib, case, False, pools=(pk.clone(), pv.clone()))
+    mix = _run(gpu_lib, case, True, pools=(pk, pv))
+    assert _same(sep, mix)
+    assert all(np.isfinite(x).all() for x in (mix[1], mix[3]))
