@@ -400,44 +400,69 @@ def pkv_sched_run(cfg: SchedConfig, fanout, suffix, out_len, filtered, device=No
 # ----------------------------------------------------------------------------------------
 # Device calls (torch tensors on the GPU)
 # ----------------------------------------------------------------------------------------
+# The tensor type and dtypes the marshalling below compares with, and torch's getter of the raw
+# current stream, looked up once: torch is imported by the first device call (the host-only
+# calls need none). Marshalling is most of a small call's host time, so it takes each tensor's
+# pointer in one check and the stream without a Stream object: an append call's host time 12.4
+# -> 7.5 us, of which its launch is 3.2.
+_torch = None
+_Tensor = None
+_raw_stream = None
+
+
+def _get_torch():
+    global _torch, _Tensor, _raw_stream
+    if _torch is None:
+        import torch
+        _Tensor = torch.Tensor
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _torch = torch
+    return _torch
+
+
 def _dev_ptr(t, name, dtype=None):
-    import torch
     if t is None:
         return None
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    torch = _torch or _get_torch()
+    if (isinstance(t, _Tensor) and t.is_cuda and (dtype is None or t.dtype is dtype)
+            and t.is_contiguous()):
+        return t.data_ptr()
+    if not isinstance(t, _Tensor) or t.device.type != "cuda":
         raise TypeError(f"{name} must be a GPU tensor (the library has no CPU path)")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    return c_void_p(t.data_ptr())
+    raise ValueError(f"{name} must be contiguous")
 
 
 def _stream(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    torch = _torch or _get_torch()
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def paged_kv(k_cache, v_cache) -> PagedKV:
     """Describe a pool: k_cache bf16 [num_blocks][Hkv][D/8][16][8], v_cache bf16
     [num_blocks][Hkv][D][16]."""
-    import torch
-    if k_cache.dim() != 5 or v_cache.dim() != 4:
+    torch = _torch or _get_torch()
+    k_shape, v_shape = k_cache.shape, v_cache.shape
+    if len(k_shape) != 5 or len(v_shape) != 4:
         raise ValueError("k_cache must be [nb][Hkv][D/8][bs][8] and v_cache [nb][Hkv][D][bs]")
-    nb, hkv, nch, bs, e = k_cache.shape
-    if e != 8 or tuple(v_cache.shape) != (nb, hkv, nch * 8, bs):
+    nb, hkv, nch, bs, e = k_shape
+    if e != 8 or v_shape != (nb, hkv, nch * 8, bs):
         raise ValueError("k_cache / v_cache shapes disagree")
-    kp = _dev_ptr(k_cache, "k_cache", torch.bfloat16)
-    vp = _dev_ptr(v_cache, "v_cache", torch.bfloat16)
-    return PagedKV(kp, vp, nb, bs, hkv, nch * 8)
+    bf16 = torch.bfloat16
+    return PagedKV(_dev_ptr(k_cache, "k_cache", bf16), _dev_ptr(v_cache, "v_cache", bf16), nb, bs,
+                   hkv, nch * 8)
 
 
 def pkv_kv_append(k_cache, v_cache, k_new, v_new, block_tables, cached_lens, cu_new_lens,
                   max_new_len: int, stream=None) -> None:
-    import torch
+    torch = _torch or _get_torch()
     kv = paged_kv(k_cache, v_cache)
-    b = int(cached_lens.shape[0])
+    b = cached_lens.shape[0]
     _check(_lib.pkv_kv_append(ctypes.byref(kv), _dev_ptr(k_new, "k_new", torch.bfloat16),
                               _dev_ptr(v_new, "v_new", torch.bfloat16),
                               _dev_ptr(block_tables, "block_tables", torch.int32),
@@ -456,10 +481,10 @@ def pkv_prefill_workspace_bytes(num_seqs, total_new, num_q_heads, num_kv_heads, 
 def pkv_prefill_attention(k_cache, v_cache, q, block_tables, cached_lens, cu_new_lens,
                           max_new_len: int, max_total_len: int, scale: float, out, lse=None,
                           workspace=None, stream=None) -> None:
-    import torch
+    torch = _torch or _get_torch()
     kv = paged_kv(k_cache, v_cache)
     t, hq, d = q.shape
-    b = int(cached_lens.shape[0])
+    b = cached_lens.shape[0]
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(_lib.pkv_prefill_attention(
         ctypes.byref(kv), _dev_ptr(q, "q", torch.bfloat16), hq,
@@ -479,7 +504,7 @@ def pkv_decode_workspace_bytes(num_seqs, num_q_heads, num_kv_heads, head_dim,
 
 def pkv_decode_attention(k_cache, v_cache, q, block_tables, seq_lens, max_seq_len: int,
                          scale: float, out, lse=None, workspace=None, stream=None) -> None:
-    import torch
+    torch = _torch or _get_torch()
     kv = paged_kv(k_cache, v_cache)
     b, hq, d = q.shape
     if workspace is None:  # convenience for one-off calls; timed callers pass their own
@@ -501,7 +526,7 @@ def pkv_decode_attention_noalloc(k_cache, v_cache, q, block_tables, seq_lens, ma
                                  scale: float, out, lse=None, stream=None) -> None:
     """pkv_decode_attention without a workspace argument: the library's fixed per-GPU
     scratch array serves instead (nothing is allocated here or in the library)."""
-    import torch
+    torch = _torch or _get_torch()
     kv = paged_kv(k_cache, v_cache)
     b, hq, d = q.shape
     _check(_lib.pkv_decode_attention_noalloc(
@@ -519,10 +544,10 @@ def pkv_mixed_attention(k_cache, v_cache, scale: float,
                         lse=None, d_lse=None, workspace=None, stream=None) -> None:
     """A prefill batch (as pkv_prefill_attention) and a decode batch (as
     pkv_decode_attention) in one fused launch."""
-    import torch
+    torch = _torch or _get_torch()
     kv = paged_kv(k_cache, v_cache)
     t, hq, d = q.shape
-    b = int(cached_lens.shape[0])
+    b = cached_lens.shape[0]
     bd = int(seq_lens.shape[0])
     if workspace is None:
         workspace = alloc_workspace(pkv_decode_workspace_bytes(bd, hq, int(k_cache.shape[1]), d,
@@ -544,7 +569,7 @@ def pkv_mixed_attention(k_cache, v_cache, scale: float,
 
 def pkv_copy_blocks(k_cache, v_cache, pairs, stream=None) -> None:
     """pairs: int32 GPU tensor [n][2] of (source block, copy)."""
-    import torch
+    torch = _torch or _get_torch()
     kv = paged_kv(k_cache, v_cache)
     if pairs.dim() != 2 or pairs.shape[1] != 2:
         raise ValueError("pairs must be [n][2]")
@@ -554,7 +579,7 @@ def pkv_copy_blocks(k_cache, v_cache, pairs, stream=None) -> None:
 
 def pkv_gather_kv(k_cache, v_cache, block_tables, lens, cu_lens, max_len: int, k_out, v_out,
                   stream=None) -> None:
-    import torch
+    torch = _torch or _get_torch()
     kv = paged_kv(k_cache, v_cache)
     _check(_lib.pkv_gather_kv(ctypes.byref(kv), _dev_ptr(block_tables, "block_tables",
                                                          torch.int32),
