@@ -63,12 +63,15 @@ constexpr int kBufferFlags = 0x00020000;
 // 16 bytes land at lds + 16 i. The buffer form, unlike the global form, leaves the
 // compiler's LDS-read wait counting exact. The builtins exist for the device target only,
 // so the body is compiled in the device pass.
+// kOffset (bytes, below 4096) moves both the source and the destination, as the instruction's
+// own offset: a run of loads then shares one offset register and one LDS base.
+template <int kOffset = 0>
 __device__ __forceinline__ void lds_load16(const void* base, int bytes, int voffset, void* lds) {
 #if __HIP_DEVICE_COMPILE__
   const __amdgpu_buffer_rsrc_t rsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, kBufferFlags);
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)lds,
-                                           16, voffset, 0, 0, 0);
+                                           16, voffset, 0, kOffset, 0);
 #endif
 }
 

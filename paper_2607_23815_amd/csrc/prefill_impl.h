@@ -107,7 +107,8 @@ struct Staging {
   static constexpr int WLOADS = UNITS / 64 / kSlabWaves;  // loads per wave per block slab
   int slab, part;  // the block of a tile this wave stages; its share of it
   // Per-lane element offsets of load 0 within a block slab; load k reads 512 k elements
-  // further on (the swizzles act within 64-unit groups), so two registers serve every load.
+  // further on (the swizzles act within 64-unit groups) and writes as far on in LDS, so it
+  // differs in the instruction's offset only and two registers serve every load.
   int kofs, vofs;
   __device__ __forceinline__ Staging(int wave, int lane) : slab(wave & 3), part(wave >> 2) {
     const int pos = part * WLOADS * 64 + lane;
@@ -118,7 +119,7 @@ struct Staging {
   }
   template <int K>
   __device__ __forceinline__ void issue_load(const uint16_t* src, uint16_t* dst, int ofs) const {
-    lds_load16(src, SLAB * 2, (ofs + K * 512) * 2, dst + slab * SLAB + (part * WLOADS + K) * 512);
+    lds_load16<K * 1024>(src, SLAB * 2, ofs * 2, dst + slab * SLAB + part * WLOADS * 512);
     if constexpr (K + 1 < WLOADS) issue_load<K + 1>(src, dst, ofs);
   }
   // This wave's share of block `blk` (kv head `kvh`) into the tile buffer `dst`, with offsets
