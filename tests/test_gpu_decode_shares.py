@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import workloads as W
-from tests.gpu_util import dev_pools, say
+from tests.gpu_util import bf16_to_f64, dev_pools, say
 from tests.test_gpu_decode import check, oracle_decode, run_decode
 from tests.test_gpu_mixed import _run, _same
 
@@ -57,3 +57,18 @@ def test_mixed_decode_shares_equal_the_decode_call(gpu_lib, c):
     mix = _run(gpu_lib, case, True, pools=(pk, pv))
     assert _same(sep, mix)
     assert all(np.isfinite(x).all() for x in (mix[1], mix[3]))
+
+
+def test_merge_keeps_an_infinite_value(gpu_lib):
+    """An infinite V element under a positive weight makes its output infinite, not NaN, also
+    where the merge of the splits reads them in groups that the last one does not fill."""
+    say("[decode shares] infinite value")
+    name, hq, hkv, d, ctx = CASES[2]
+    case = _case(CASES[2])
+    b = case.batches[0]
+    dim, i = 7, ctx.index(2047)  # two splits of 1024 keys
+    case.pool_v[b.block_tables[i, 0], :, dim, 5] = 0x7F80  # +inf at key 5 of every kv head
+    out = bf16_to_f64(run_decode(gpu_lib, case)[0])
+    assert np.all(np.isposinf(out[i, :, dim]))
+    out[i, :, dim] = 0.0
+    assert np.isfinite(out).all()
