@@ -277,7 +277,7 @@ pkv_status pkv_kv_append(const pkv_paged_kv* kv, const void* k_new, const void* 
  * cut points depend on key positions and host arguments only, so results are
  * deterministic. Order (optional, the same workspace): a batch of more than one sequence
  * whose keys reach 8192 (max_total_len >= 8192) takes its sequences longest first (a small
- * kernel writes the order into the workspace), so the launch does not end on a few long
+ * kernel writes the order into the workspace; few sequences are ranked in the launch), so the launch does not end on a few long
  * items; the order moves work items, not arithmetic, so the results are bit-identical to
  * the unordered launch. With workspace NULL (or when the size is 0) the launch neither
  * splits nor orders; a non-NULL workspace smaller than the size is refused. Calls sharing a

@@ -259,8 +259,13 @@ DecodePlan decode_plan(const KvView& kv, int32_t hq, int32_t num_seqs, int32_t m
   // Longest first pays where not every wave is resident at once and the batch is long against
   // the ordering launch (4.5 us): 256 sequences of 256-4096 keys 383 us against 399, 256 of
   // 400-1200 154 against 156, but 200 of 50-300 30 against 27.
-  p.ordered = p.items * p.parts > kWaveSlots &&
-              groups * max_seq_len * kv.head_dim * 4 >= (int64_t)kOrderBytes;
+  // Up to 64 sequences the waves find the order themselves (48 of 256-4096 keys, 64/8 heads:
+  // 79.1 us against 81.2; 60 of 400-8000, 8/8 heads 176.4 against 177.6; short batches, which
+  // take no order, would lose 2-3 us by it).
+  const bool longest_first = p.items * p.parts > kWaveSlots &&
+                             groups * max_seq_len * kv.head_dim * 4 >= (int64_t)kOrderBytes;
+  p.by_rank = longest_first && num_seqs <= kRankSeqs;
+  p.ordered = longest_first && !p.by_rank;
   p.order = static_cast<int32_t*>(workspace);
   p.ws_o = nullptr;
   p.ws_ml = nullptr;

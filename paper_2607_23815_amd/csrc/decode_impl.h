@@ -11,7 +11,8 @@
 // bandwidth bounds a large batch (512 sequences of 512-2048 keys: 5.9 TB/s), the chain of
 // dependent loads (length, table, first K/V) and the launches a small one (one sequence of
 // 800 keys with its append: 15.8 us as ordering + 64-key splits + merge launches, 11.3 us as
-// one). A long batch is taken longest first (a small ordering kernel runs before the launch).
+// one). A long batch is taken longest first (past 64 sequences an ordering kernel runs before the
+// launch, up to 64 every wave ranks the lengths for itself).
 // A wave streams 32 keys (two 16-token blocks) at a time straight from HBM into the
 // matrix-core operands:
 //   scores  S^T[32 keys][16 cols] = K[keys][D] . Q^T[D][cols]      (v_mfma 16x16x32 bf16)
@@ -249,7 +250,8 @@ __device__ __forceinline__ void decode_load_q(const uint16_t* __restrict__ q, in
 // split starts inside the table, so no split is empty.
 struct DecodeWork {
   const int32_t* seq_lens;
-  const int32_t* order;  // sequences longest first, or null: in batch order
+  const int32_t* order;  // sequences longest first, or null: see by_rank
+  bool by_rank;          // without an order: each wave ranks the lengths (else: batch order)
   int32_t num_seqs;
   int32_t split_keys, max_splits, max_keys;
 };
@@ -263,7 +265,9 @@ __device__ __forceinline__ bool decode_item(const DecodeWork& w, int32_t hkv, in
   const int64_t per_seq = (int64_t)hkv * w.max_splits;
   const int rank = (int)(item / per_seq);
   if (rank >= w.num_seqs) return false;
-  it.i = w.order != nullptr ? w.order[rank] : rank;
+  it.i = w.order != nullptr ? w.order[rank]
+         : w.by_rank        ? seq_at_rank(w.seq_lens, nullptr, w.num_seqs, rank)
+                            : rank;
   const int rem = (int)(item % per_seq);
   it.kvh = rem / w.max_splits;
   it.sp = rem % w.max_splits;

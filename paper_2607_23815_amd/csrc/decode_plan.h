@@ -8,7 +8,7 @@ namespace pkv {
 
 inline dec::DecodeWork decode_work(const DecodePlan& p, const int32_t* seq_lens,
                                    int32_t num_seqs) {
-  return dec::DecodeWork{seq_lens, p.ordered ? p.order : nullptr, num_seqs,
+  return dec::DecodeWork{seq_lens, p.ordered ? p.order : nullptr, p.by_rank, num_seqs,
                          p.split,  p.max_splits,                  p.max_keys};
 }
 

@@ -65,7 +65,9 @@ struct DecodePlan {
   int32_t split, max_splits;
   int32_t parts;     // waves' shares per work item (1: one wave is the item)
   int32_t max_keys;  // lengths are cut to it
-  bool ordered;      // the launch takes its sequences longest first
+  // The launch takes its sequences longest first, by an order written before it (ordered) or
+  // by each wave's ranking of the lengths (by_rank; at most 64 sequences).
+  bool ordered, by_rank;
   int32_t* order;
   float* ws_o;
   float* ws_ml;

@@ -22,12 +22,12 @@ void prefill_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     int32_t hkv, int32_t num_blocks, int32_t qtiles, float scale_log2,
                     uint16_t* __restrict__ out, float* __restrict__ lse, int32_t split_keys,
                     int32_t nsplit, float* __restrict__ ws_o, float* __restrict__ ws_ml,
-                    const int32_t* __restrict__ order) {
+                    const int32_t* __restrict__ order, bool by_rank) {
   __shared__ __align__(16) pre::PrefillSmem<D> sm;
   if constexpr (kPlan)
     pre::prefill_body<D>(q, k_cache, v_cache, block_tables, max_blocks, cached_lens,
                          cu_new_lens, num_seqs, hq, hkv, num_blocks, qtiles, scale_log2, out,
-                         lse, blockIdx.x, sm, split_keys, nsplit, ws_o, ws_ml, order);
+                         lse, blockIdx.x, sm, split_keys, nsplit, ws_o, ws_ml, order, by_rank);
   else
     pre::prefill_body<D>(q, k_cache, v_cache, block_tables, max_blocks, cached_lens,
                          cu_new_lens, num_seqs, hq, hkv, num_blocks, qtiles, scale_log2, out,
@@ -71,11 +71,17 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(
   float acc[PER];
 #pragma unroll
   for (int e = 0; e < PER; ++e) acc[e] = 0.f;
-  for (int s = 0; s <= last; ++s) {
-    const float ws = __shfl(w, s);
-    const float* src = ws_o + (slot0 + s) * D + lane * PER;
+  const float* src = ws_o + slot0 * D + lane * PER;
+  // eight splits' loads at a time; past the last one its own again, taken as zeros (a zero
+  // weight would turn its infinities into NaN)
+  for (int s = 0; s <= last; s += 8) {
 #pragma unroll
-    for (int e = 0; e < PER; ++e) acc[e] += ws * src[e];
+    for (int k = 0; k < 8; ++k) {
+      const float ws = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), s + k));
+      const float* from = src + (size_t)min(s + k, last) * D;
+#pragma unroll
+      for (int e = 0; e < PER; ++e) acc[e] += ws * (s + k <= last ? from[e] : 0.f);
+    }
   }
   uint16_t* dst = out + ((size_t)(row0 + j) * hq + h) * D + lane * PER;
   if constexpr (PER == 2) {
@@ -101,6 +107,7 @@ constexpr int32_t kMaxSplits = 64;
 // kernel and one more dependent load per workgroup): with documents up to 16k keys the
 // longest items would otherwise start anywhere in the launch and extend its end.
 constexpr int32_t kOrderKeys = 8192;
+constexpr int32_t kRankSeqsPrefill = 16;  // at most kRankSeqs
 
 PrefillSplit prefill_split_plan(int32_t num_seqs, int32_t hq, int32_t hkv, int32_t max_new_len,
                                 int32_t max_total_len) {
@@ -142,7 +149,13 @@ hipError_t launch_prefill(const KvView& kv, const uint16_t* q, int32_t hq,
   float* ws_o = nullptr;
   float* ws_ml = nullptr;
   char* ws = static_cast<char*>(workspace);
-  if (sp.order) {
+  // Few sequences are ranked by each wave for itself (the order's place stays unused): 2 of
+  // 9-20k keys 113.2 us against 116.8; at 64 the ranking in every workgroup of a long launch
+  // costs more than the ordering launch (1708 us against 1686).
+  const bool by_rank = sp.order && num_seqs <= kRankSeqsPrefill;
+  if (by_rank) {
+    ws += order_bytes(num_seqs);
+  } else if (sp.order) {
     order = reinterpret_cast<int32_t*>(ws);
     ws += order_bytes(num_seqs);
     const hipError_t err = launch_seq_order(cached_lens, cu_new_lens, num_seqs, order, stream);
@@ -163,7 +176,7 @@ hipError_t launch_prefill(const KvView& kv, const uint16_t* q, int32_t hq,
   hipLaunchKernelGGL(kern, grid, dim3(pre::kThreads), 0, stream, q, kv.k, kv.v, block_tables,
                      max_blocks, cached_lens, cu_new_lens, num_seqs, hq, kv.hkv, kv.num_blocks,
                      (int32_t)qtiles, scale_log2, out, lse, sp.split_keys, sp.nsplit, ws_o,
-                     ws_ml, order);
+                     ws_ml, order, by_rank);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess || sp.nsplit <= 1) return err;
   const dim3 mgrid((unsigned)(((int64_t)max_new_len * hq + 3) / 4), (unsigned)num_seqs);

@@ -641,7 +641,7 @@ __device__ __forceinline__ void prefill_body(const uint16_t* __restrict__ q, con
                     uint16_t* __restrict__ out, float* __restrict__ lse, const unsigned wg,
                     PrefillSmem<D>& sm, int32_t split_keys = 0, int32_t nsplit = 1, float* __restrict__ ws_o = nullptr,
                     float* __restrict__ ws_ml = nullptr,
-                    const int32_t* __restrict__ order = nullptr) {
+                    const int32_t* __restrict__ order = nullptr, const bool by_rank = false) {
   // XCD-aware mapping: workgroup id b runs on XCD b % 8 (a mixed launch passes a `wg` with
   // the same residue mod 8 as its workgroup id). The unit that must stay on one XCD
   // is a (sequence, kv head) group -- its query tiles read the same K/V and share that XCD's
@@ -665,8 +665,10 @@ __device__ __forceinline__ void prefill_body(const uint16_t* __restrict__ q, con
   const int sp = idx % nsplit;
   if (group >= num_seqs * hkv) return;
   const int kvh = group % hkv;
-  // with an order, group ranks map to sequences longest first
-  const int i = order != nullptr ? order[group / hkv] : group / hkv;
+  // with an order (or by_rank, at most kRankSeqs sequences), group ranks map to sequences longest first
+  const int i = order != nullptr ? order[group / hkv]
+                : by_rank        ? seq_at_rank(cached_lens, cu_new_lens, num_seqs, group / hkv)
+                                 : group / hkv;
   // The first table chunk (entry `lane` of the sequence's row, and entry 0) is fetched
   // before the lengths: its address depends on the sequence only, so the two loads overlap.
   const int32_t* table = block_tables + (size_t)i * max_blocks;

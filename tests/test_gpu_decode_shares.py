@@ -26,6 +26,9 @@ CASES = [
     ("one_wave", 64, 64, 64, [511, 510, 0, 1, 16, 31, 32, 33] + [7] * 24),
     # the same pairs with one key more: four shares
     ("one_wave_edge", 64, 64, 64, [512, 511, 0, 1, 16, 31, 32, 33] + [7] * 24),
+    # longest first, the order found by the waves (64 sequences) and by a launch (65)
+    ("ranked_64", 32, 32, 128, [600, 0, 5, 5, 17, 599] + [9 + k % 7 for k in range(58)]),
+    ("ordered_65", 32, 32, 128, [600, 0, 5, 5, 17, 599] + [9 + k % 7 for k in range(59)]),
 ]
 
 
