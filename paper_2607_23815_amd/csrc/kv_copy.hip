@@ -187,10 +187,18 @@ __global__ __launch_bounds__(256) void gather_kv_kernel(
 
 }  // namespace
 
-hipError_t launch_kv_append(const KvView& kv, const uint16_t* k_new, const uint16_t* v_new,
+hipError_t launch_kv_append(const KvView& view, const uint16_t* k_new, const uint16_t* v_new,
                             const int32_t* block_tables, int32_t max_blocks,
                             const int32_t* cached_lens, const int32_t* cu_new_lens,
                             int32_t num_seqs, int32_t max_new_len, hipStream_t stream) {
+  // Two neighbouring heads of 64 dims are laid out, in the rows and in the pool, as one head of
+  // 128: moved as such, every thread of a workgroup has a chunk (with one head of 64 half of
+  // them idle). 255 sequences of 16-64 tokens, 8 heads: 11.7 us as heads of 64, 9.6 as of 128.
+  KvView kv = view;
+  if (kv.head_dim == 64 && kv.hkv % 2 == 0) {
+    kv.head_dim = 128;
+    kv.hkv /= 2;
+  }
   if (max_new_len == 1) {  // one token per sequence (a decode step)
     const dim3 tgrid(kv.hkv, num_seqs);
     if (kv.head_dim == 128)

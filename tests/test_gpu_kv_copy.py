@@ -119,3 +119,28 @@ def test_append_one_token_per_sequence(gpu_lib, hq, hkv, d):
                                     b.cu_new_lens, b.k_new, b.v_new, 16)
     assert np.array_equal(to_host_bits(pk), ref_k)
     assert np.array_equal(to_host_bits(pv), ref_v)
+
+
+@pytest.mark.parametrize("tokens", [1, 40])
+@pytest.mark.parametrize("hkv", [1, 2, 3, 6])
+def test_append_head_dim_64_odd_and_even_heads(gpu_lib, hkv, tokens):
+    """Heads of 64 dims move in pairs when their number is even, else one by one: bit-exact over
+    the whole pool, with blocks filled from, up to and within their middle."""
+    import torch
+    lib = gpu_lib
+    say(f"[append] head_dim 64, {hkv} kv heads, up to {tokens} tokens")
+    prefixes = [0, 5, 15, 16, 31, 100, 7, 8]
+    news = [min(n, tokens) for n in (40, 0, 1, 16, 33, 12, 9, 8)]
+    spec = W.WorkloadSpec(f"append_d64_{hkv}", 97 + hkv, hkv, hkv, 64,
+                          (W.BatchSpec("prefill", len(prefixes), W.Dist.const(1),
+                                       W.Dist.const(1)),), ("scale", 1.5))
+    case = W.make_case(spec, prefix_override=[prefixes], new_override=[news])
+    b = case.batches[0]
+    pk, pv = dev_pools(case)
+    db = DevBatch(b)
+    lib.pkv_kv_append(pk, pv, db.k_new, db.v_new, db.tables, db.cached, db.cu, db.max_new)
+    torch.cuda.synchronize()
+    ref_k, ref_v = oracle.kv_append(case.pool_k, case.pool_v, b.block_tables, b.prefix_lens,
+                                    b.cu_new_lens, b.k_new, b.v_new, 16)
+    assert np.array_equal(to_host_bits(pk), ref_k)
+    assert np.array_equal(to_host_bits(pv), ref_v)

@@ -6,7 +6,7 @@ its GPU time must be measured."""
 import numpy as np
 import pytest
 
-from tests.gpu_util import say
+from tests.gpu_util import say, to_host_bits
 from workloads.pipelines import PIPELINES, make_pipeline
 
 pytestmark = pytest.mark.gpu
@@ -91,7 +91,7 @@ def test_device_mode_results_match_the_oracle(gpu_lib, pidx, policy, budget):
     it was before the append, within the attention bar."""
     import oracle
     import torch
-    from tests.gpu_util import bf16_to_f64, compare, to_host_bits
+    from tests.gpu_util import bf16_to_f64, compare
     lib = gpu_lib
     spec = PIPELINES[pidx]
     say(f"[sched device vs oracle] {spec.name} policy {policy} step budget {budget}")
@@ -164,3 +164,26 @@ def test_device_mode_results_match_the_oracle(gpu_lib, pidx, policy, budget):
         f"{checked[False]}, decode {checked[True]}; gpu {st['gpu_ms']:.2f} ms")
     assert not failures, failures
     assert checked[False] >= 1 and checked[True] >= 1
+
+
+@pytest.mark.parametrize("budget", [0, 200])
+def test_device_mode_pool_does_not_depend_on_the_waits(gpu_lib, budget):
+    """Without a hook a run waits only when it takes a metadata slot again, with one after every
+    group: the pool ends with the same bits (many more steps than slots, block copies and
+    fused launches among them)."""
+    import torch
+    lib = gpu_lib
+    say(f"[sched device] with and without a hook, step budget {budget}")
+    d = make_pipeline(PIPELINES[1].scaled(24))
+    cfg = lib.sched_config(0, 1500, max_out=64, initial_bound=[8] * len(d["suffix"]),
+                           max_batch=16, pinning=1, max_step_tokens=budget)
+    args = (d["fanout"], d["suffix"], d["out_len"], d["filtered"])
+    pools = []
+    for hook in (None, lambda g: None):
+        dev = _device(torch, 1500, seed=5)
+        st, _, _ = lib.pkv_sched_run(cfg, *args, device=dev, group_hook=hook)
+        torch.cuda.synchronize()
+        assert st["steps"] > 16 and st["cow_copies"] > 0 and st["gpu_ms"] > 0.0
+        pools.append((to_host_bits(dev["k_cache"]), to_host_bits(dev["v_cache"])))
+    assert np.array_equal(pools[0][0], pools[1][0])
+    assert np.array_equal(pools[0][1], pools[1][1])
