@@ -1,7 +1,8 @@
 // Mixed prefill + decode attention for gfx950: one fused launch in which some workgroups run
-// prefill work items (the matrix-core-bound body of prefill_impl.h) and others run four
-// decode work items, one per wave (the HBM-bound body of decode_impl.h), so that each compute
-// unit overlaps the two kinds of work instead of running them one launch after the other.
+// prefill work items (the matrix-core-bound body of prefill_impl.h) and others decode work (the
+// HBM-bound bodies of decode_impl.h: one item shared by the four waves, or four one-wave items,
+// as the decode plan says), so that each compute unit overlaps the two kinds of work instead of
+// running them one launch after the other.
 //
 // Workgroup b runs on XCD b % 8. Each XCD's list of positions b / 8 is dealt between prefill
 // and decode workgroups in proportion to their counts, spread evenly along the list; a
