@@ -3,7 +3,6 @@
 // bodies are in decode_impl.h.
 #include <math.h>
 
-#include <algorithm>
 #include <mutex>
 
 #include "decode_impl.h"
@@ -158,10 +157,6 @@ __global__ __launch_bounds__(kOrderThreads) void decode_order_kernel(
 }
 
 
-// Waves of the decode kernels that the chip holds at once (two on each of 256 x 4 SIMDs).
-constexpr int64_t kWaveSlots = 2048;
-// Work items past which a launch stays at one wave each (a grid holds 2^32 threads).
-constexpr int64_t kMaxWideItems = int64_t(1) << 20;
 // KV bytes (at the host's longest length) from which a decode is ordered longest first.
 constexpr int64_t kOrderBytes = int64_t(512) << 20;
 
@@ -193,20 +188,6 @@ hipError_t decode_scratch(void** ptr) {
   return hipSuccess;
 }
 
-int32_t decode_split_keys(int32_t num_seqs, int32_t hkv, int32_t max_seq_len) {
-  // The finest cut a call may be planned with, which its workspace is sized for: 4096 keys,
-  // halved while a grid of one-wave items would hold fewer than 2048 waves. A function of the
-  // call's sizes only, so a given call always needs the same workspace.
-  int32_t split = 4096;
-  while (split > 64) {
-    const int64_t waves =
-        (int64_t)num_seqs * hkv * ((max_seq_len + split - 1) / split);
-    if (waves >= 2048) break;
-    split /= 2;
-  }
-  return split;
-}
-
 size_t decode_workspace_bytes(int32_t num_seqs, int32_t hq, int32_t hkv, int32_t head_dim,
                               int32_t max_seq_len) {
   const int32_t split = decode_split_keys(num_seqs, hkv, max_seq_len);
@@ -218,44 +199,9 @@ size_t decode_workspace_bytes(int32_t num_seqs, int32_t hq, int32_t hkv, int32_t
 }
 
 DecodePlan decode_plan(const KvView& kv, int32_t hq, int32_t num_seqs, int32_t max_seq_len,
-                       void* workspace) {
-  DecodePlan p;
-  // What the workspace holds, and where over-long lengths are cut: the plan below never makes
-  // more splits than decode_split_keys does.
-  const int32_t base_split = decode_split_keys(num_seqs, kv.hkv, max_seq_len);
-  p.max_keys = (max_seq_len + base_split - 1) / base_split * base_split;
-  // (sequence, kv head) pairs: the least number of work items
+                       int32_t max_blocks, void* workspace) {
+  DecodePlan p{decode_cut(num_seqs, kv.hkv, max_seq_len, max_blocks)};
   const int64_t groups = (int64_t)num_seqs * kv.hkv;
-  // Shares per item. Cutting an item between the waves of one workgroup costs one LDS merge
-  // and no launch, and evens out the waves' lengths, so four shares are the rule. Eight pay
-  // where four would leave wave slots empty and some sequences are long enough to run on
-  // alone (48 sequences of 256-4096 keys, 64/8 heads: 84 us against 104; at 512 pairs and up
-  // four are better: 64 sequences of 200-1000 keys 28 us against 31). One wave per item is
-  // left where the pairs alone fill the chip and a share would be a step or two (512 sequences
-  // of at most 128 keys: 38 us against 48; the two meet at 600 keys).
-  int64_t target;  // waves aimed at
-  if ((groups >= kWaveSlots && max_seq_len <= 512) || groups >= kMaxWideItems) {
-    p.parts = 1;
-    target = 1;
-  } else if (groups < kWaveSlots / 4 && max_seq_len >= 2048) {
-    p.parts = 8;
-    target = kWaveSlots;
-  } else {
-    p.parts = 4;
-    target = kWaveSlots / 2;
-  }
-  // Splits across workgroups cost partial results and a merge launch (about 4 us), so they are
-  // made only while the items leave the chip without enough loads in flight, and of at least
-  // 1024 keys (4 sequences of 24-32k keys, 32/8 heads: 87 us, at 1.6 times fewer or 2 times
-  // more splits 92-104; one sequence of 800 keys: unsplit 11.3 us with its append, two
-  // splits 12.4). At most 16384 keys, so that one long sequence does not outlast the rest.
-  const int64_t want = std::max<int64_t>(1, target / (groups * p.parts));
-  int64_t split = std::max<int64_t>((p.max_keys + want - 1) / want, 1024);
-  split = std::max<int64_t>(std::min<int64_t>(split, 16384), base_split);
-  const int64_t unit = 32 * p.parts;
-  p.split = (int32_t)((split + unit - 1) / unit * unit);
-  p.max_splits = (p.max_keys + p.split - 1) / p.split;
-  p.items = groups * p.max_splits;
   // Longest first pays where not every wave is resident at once and the batch is long against
   // the ordering launch (4.5 us): 256 sequences of 256-4096 keys 383 us against 399, 256 of
   // 400-1200 154 against 156, but 200 of 50-300 30 against 27.
@@ -313,7 +259,7 @@ hipError_t launch_decode(const KvView& kv, const uint16_t* q, int32_t hq,
                          const int32_t* seq_lens, int32_t num_seqs, int32_t max_seq_len,
                          float scale, uint16_t* out, float* lse, void* workspace,
                          hipStream_t stream) {
-  const DecodePlan p = decode_plan(kv, hq, num_seqs, max_seq_len, workspace);
+  const DecodePlan p = decode_plan(kv, hq, num_seqs, max_seq_len, max_blocks, workspace);
   if (p.items > INT32_MAX) return hipErrorInvalidValue;
   const dim3 grid((unsigned)p.items);
   const float scale_log2 = scale * kLog2e;

@@ -243,11 +243,10 @@ __device__ __forceinline__ void decode_load_q(const uint16_t* __restrict__ q, in
 
 // A decode launch's work list. Work item = (sequence rank, kv head, split); a sequence is cut
 // into splits of split_keys keys, and an item's keys into `parts` shares, one per wave
-// (parts = 1: one wave is the item). max_keys bounds every length (see decode_plan): a length
-// above it breaks the caller's contract and is cut to it (the merge cuts it the same way),
-// and keys past the table are not attended, so such a call computes over fewer keys but never
-// leaves its workspace. With max_seq_len <= max_blocks * 16 (checked on the host) every
-// split starts inside the table, so no split is empty.
+// (parts = 1: one wave is the item). max_keys bounds every length (see decode_cut): a length
+// above it breaks the caller's contract and is cut to it (the merge cuts it the same way), so
+// such a call computes over fewer keys but never leaves its workspace or the table. A cut
+// length's splits all start below it, so no split is empty.
 struct DecodeWork {
   const int32_t* seq_lens;
   const int32_t* order;  // sequences longest first, or null: see by_rank
@@ -260,8 +259,8 @@ struct DecodeItem {
 };
 // false: nothing to do (past the list, or past the sequence's splits; 0 splits for a length
 // below 1: no output)
-__device__ __forceinline__ bool decode_item(const DecodeWork& w, int32_t hkv, int32_t max_blocks,
-                                            int64_t item, DecodeItem& it) {
+__device__ __forceinline__ bool decode_item(const DecodeWork& w, int32_t hkv, int64_t item,
+                                            DecodeItem& it) {
   const int64_t per_seq = (int64_t)hkv * w.max_splits;
   const int rank = (int)(item / per_seq);
   if (rank >= w.num_seqs) return false;
@@ -276,7 +275,6 @@ __device__ __forceinline__ bool decode_item(const DecodeWork& w, int32_t hkv, in
   if (it.sp >= it.nsplit) return false;
   it.k0 = it.sp * w.split_keys;
   it.k1 = min(len, it.k0 + w.split_keys);
-  if ((it.k1 - 1) / kBlockSize >= max_blocks) it.k1 = max_blocks * kBlockSize;  // (no overflow)
   return true;
 }
 
@@ -294,7 +292,7 @@ __device__ __forceinline__ void decode_body(
   const int col = lane & 15;   // query head within the kv group (column)
   const int grp = lane >> 4;   // lane group 0..3
   DecodeItem it;
-  if (!decode_item(work, hkv, max_blocks, item, it)) return;
+  if (!decode_item(work, hkv, item, it)) return;
   const int i = it.i;
   const int h = it.kvh * g + col;
   bf16x8 qf[D / 32];
@@ -355,7 +353,7 @@ __device__ __forceinline__ void decode_group_body(
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   DecodeItem it;
-  if (!decode_item(work, hkv, max_blocks, item, it)) return;  // (workgroup-uniform)
+  if (!decode_item(work, hkv, item, it)) return;  // (workgroup-uniform)
   const int share = ((it.k1 - it.k0 + kParts - 1) / kParts + 31) / 32 * 32;
   bf16x8 qf[D / 32];
   decode_load_q<D>(q, it.i, hq, g, it.kvh, qf);

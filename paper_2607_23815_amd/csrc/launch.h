@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "decode_cut.h"
+
 namespace pkv {
 
 struct KvView {
@@ -54,27 +56,21 @@ hipError_t launch_prefill(const KvView& kv, const uint16_t* q, int32_t hq,
                           int32_t max_total_len, float scale, uint16_t* out, float* lse,
                           void* workspace, hipStream_t stream);
 
-// Decode: the shortest splits (a multiple of 32 keys) the workspace has room for.
-int32_t decode_split_keys(int32_t num_seqs, int32_t hkv, int32_t max_seq_len);
 size_t decode_workspace_bytes(int32_t num_seqs, int32_t hq, int32_t hkv, int32_t head_dim,
                               int32_t max_seq_len);
-// The pieces of a decode launch, shared with the mixed launch: the split plan and the
+// The pieces of a decode launch, shared with the mixed launch: the cut into work items and the
 // workspace layout (the sequence order, then the splits' partial results), the ordering
 // kernel, and the merge of partial results (nothing when no sequence splits).
-struct DecodePlan {
-  int32_t split, max_splits;
-  int32_t parts;     // waves' shares per work item (1: one wave is the item)
-  int32_t max_keys;  // lengths are cut to it
+struct DecodePlan : DecodeCut {
   // The launch takes its sequences longest first, by an order written before it (ordered) or
   // by each wave's ranking of the lengths (by_rank; at most 64 sequences).
   bool ordered, by_rank;
   int32_t* order;
   float* ws_o;
   float* ws_ml;
-  int64_t items;  // (sequence, kv head, split) work items
 };
 DecodePlan decode_plan(const KvView& kv, int32_t hq, int32_t num_seqs, int32_t max_seq_len,
-                       void* workspace);
+                       int32_t max_blocks, void* workspace);
 // (nothing when the plan does not order)
 hipError_t launch_decode_order(const DecodePlan& p, const int32_t* seq_lens, int32_t num_seqs,
                                hipStream_t stream);

@@ -74,7 +74,7 @@ hipError_t launch_mixed(const KvView& kv, int32_t hq, float scale, const uint16_
                         const int32_t* seq_lens, int32_t d_num_seqs, int32_t max_seq_len,
                         uint16_t* d_out, float* d_lse, void* workspace, hipStream_t stream) {
   const pre::PrefillGrid pg = pre::prefill_grid(hq, kv.hkv, num_seqs, max_new_len);
-  const DecodePlan dp = decode_plan(kv, hq, d_num_seqs, max_seq_len, workspace);
+  const DecodePlan dp = decode_plan(kv, hq, d_num_seqs, max_seq_len, d_max_blocks, workspace);
   const int64_t d_wgs =
       dp.parts == 1 ? (dp.items + kDecodePerWg - 1) / kDecodePerWg : dp.items;
   const int64_t p8 = pg.items / 8;  // a multiple of 8 by construction

@@ -1,0 +1,106 @@
+"""CPU tier: how a decode call is cut into work items (csrc/decode_cut.h, host arithmetic alone),
+compiled here with the host compiler and swept over the sizes: every split and share that the
+kernels form from a sequence's length has keys, lies inside the block table's row, and has a place
+in the workspace, also for lengths above the host's max_seq_len."""
+import ctypes
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2607_23815_amd", "csrc")
+
+SOURCE = """
+#include "decode_cut.h"
+extern "C" void cut(int32_t num_seqs, int32_t hkv, int32_t max_seq_len, int32_t max_blocks,
+                    int64_t* out) {
+  const pkv::DecodeCut c = pkv::decode_cut(num_seqs, hkv, max_seq_len, max_blocks);
+  out[0] = c.split; out[1] = c.max_splits; out[2] = c.parts; out[3] = c.max_keys;
+  out[4] = c.items; out[5] = pkv::decode_split_keys(num_seqs, hkv, max_seq_len);
+}
+"""
+
+
+class Cut:
+    def __init__(self, v):
+        (self.split, self.max_splits, self.parts, self.max_keys, self.items,
+         self.base_split) = (int(x) for x in v)
+
+
+@pytest.fixture(scope="module")
+def cut(tmp_path_factory):
+    gxx = shutil.which("g++") or shutil.which("c++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    d = tmp_path_factory.mktemp("cut")
+    src, so = d / "cut.cpp", d / "cut.so"
+    src.write_text(SOURCE)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC,
+                    "-o", str(so), str(src)], check=True)
+    fn = ctypes.CDLL(str(so)).cut
+
+    def call(num_seqs, hkv, max_seq_len, max_blocks=None):
+        out = (ctypes.c_int64 * 6)()
+        fn(num_seqs, hkv, max_seq_len,
+           -(-max_seq_len // 16) if max_blocks is None else max_blocks, out)
+        return Cut(out)
+    return call
+
+
+def _splits(c, length):
+    """The (first key, end) of each split the kernels form for a sequence of this length."""
+    n = min(length, c.max_keys)
+    return [(s * c.split, min(n, (s + 1) * c.split)) for s in range(-(-n // c.split))]
+
+
+def _check(c, num_seqs, hkv, max_seq_len, max_blocks):
+    what = (num_seqs, hkv, max_seq_len, max_blocks)
+    assert c.parts in (1, 4, 8) and c.split % (32 * c.parts) == 0, what
+    assert c.items == num_seqs * hkv * c.max_splits, what
+    # the workspace is sized for splits of base_split keys
+    assert c.max_splits <= -(-max_seq_len // c.base_split), what
+    assert c.max_keys >= max_seq_len, what
+    rounded = -(-max_seq_len // c.base_split) * c.base_split
+    for length in (1, max_seq_len - 1, max_seq_len, max_seq_len + 1, c.max_keys, rounded,
+                   rounded + 1, max_blocks * 16, max_blocks * 16 + 5, 2 * max_seq_len):
+        if length < 1:
+            continue
+        splits = _splits(c, length)
+        assert len(splits) <= c.max_splits, (what, length)
+        # a length above max_seq_len is cut to the workspace's rounding of it and to the table
+        assert splits[-1][1] == min(length, rounded, max_blocks * 16), (what, length)
+        for k0, k1 in (splits[0], splits[-1]):
+            assert 0 <= k0 < k1 <= max_blocks * 16, (what, length, k0, k1)
+            share = ((k1 - k0 + c.parts - 1) // c.parts + 31) // 32 * 32
+            assert share >= 32 and 1 <= -(-(k1 - k0) // share) <= c.parts, (what, length)
+
+
+def test_splits_have_keys_inside_the_table(cut):
+    rnd = random.Random(0)
+    # a last split that would start past the table's row: splits of 4352 keys, lengths rounded
+    # to 512 (134912 = 31 x 4352 lies between 8417 x 16 = 134672 and 135168 = 264 x 512)
+    c = cut(1, 8, 134672, 8417)
+    assert c.split == 4352 and c.base_split == 512
+    sizes = [(1, 8, 134672, 8417), (9, 1, 117264, 7329), (1, 8, 300, 19), (256, 8, 4096, 256)]
+    for _ in range(20000):
+        hkv = rnd.choice([1, 2, 4, 8, 16, 32, 64])
+        num_seqs = int(2 ** rnd.uniform(0, 12))
+        max_seq_len = int(2 ** rnd.uniform(0, 20))
+        blocks = -(-max_seq_len // 16) + rnd.choice([0, 0, 1, 7, 300, 1 << 20])
+        sizes.append((num_seqs, hkv, max_seq_len, blocks))
+    for s in sizes:
+        _check(cut(*s), *s)
+
+
+def test_split_size_does_not_depend_on_the_table_width(cut):
+    """A wider table (rows padded for longer sequences) leaves the cut of the same lengths."""
+    rnd = random.Random(1)
+    for _ in range(2000):
+        num_seqs, hkv = int(2 ** rnd.uniform(0, 10)), rnd.choice([1, 2, 8])
+        n = int(2 ** rnd.uniform(0, 18))
+        a, b = cut(num_seqs, hkv, n), cut(num_seqs, hkv, n, 1 << 16)
+        assert (a.split, a.parts) == (b.split, b.parts)
+        assert _splits(a, n) == _splits(b, n)

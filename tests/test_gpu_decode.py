@@ -8,7 +8,7 @@ import pytest
 import oracle
 import workloads as W
 from tests.gpu_util import (DevBatch, bf16_to_f64, compare, dev_pools, i32, say, scale_for,
-                            to_host_bits)
+                            to_dev_bits, to_host_bits)
 from tests.test_gpu_prefill import LSE_MAX, LSE_MEAN
 
 pytestmark = pytest.mark.gpu
@@ -164,6 +164,37 @@ def test_decode_over_long_length_is_cut_to_the_planned_splits(gpu_lib, hq, hkv, 
     torch.cuda.synchronize()
     ref = _oracle_first_keys(case, b, np.minimum(lens, cut), scale_for(d))
     check(spec.name, (to_host_bits(out), lse.cpu().numpy().astype(np.float64)), ref)
+
+
+@pytest.mark.parametrize("length", [134672, 134913, 140000])
+def test_decode_over_long_length_where_splits_are_no_multiple_of_the_rounding(gpu_lib, length):
+    """One sequence over a table row of 8417 blocks: splits of 4352 keys in a workspace sized by
+    512-key splits, so the 32nd split would start past the row's 134672 keys. A longer length is
+    cut to the row; the blocks repeat, so that the pool stays small."""
+    import torch
+    say(f"[decode] length {length} over a row of 134672 keys")
+    hkv = hq = 8
+    d, blocks, max_len = 64, 8417, 8417 * 16
+    rng = np.random.default_rng(163)
+    pool_k = W.f32_to_bf16_bits(rng.standard_normal((40, hkv, d // 8, 16, 8)).astype(np.float32))
+    pool_v = W.f32_to_bf16_bits(rng.standard_normal((40, hkv, d, 16)).astype(np.float32))
+    q = W.f32_to_bf16_bits(1.25 * rng.standard_normal((1, hq, d)).astype(np.float32))
+    table = rng.integers(0, 40, (1, blocks)).astype(np.int32)
+    out = torch.empty((1, hq, d), dtype=torch.bfloat16, device="cuda")
+    lse = torch.empty((1, hq), dtype=torch.float32, device="cuda")
+    ws = gpu_lib.alloc_workspace(gpu_lib.pkv_decode_workspace_bytes(1, hq, hkv, d, max_len))
+    gpu_lib.pkv_decode_attention(to_dev_bits(pool_k), to_dev_bits(pool_v), to_dev_bits(q),
+                                 i32(table), i32([length]), max_len, scale_for(d), out, lse=lse,
+                                 workspace=ws)
+    torch.cuda.synchronize()
+    kc, vc = oracle.gather_seq(pool_k, pool_v, table[0], max_len, 16)
+    kf, vf = oracle.bf16_bits_to_f64(kc), oracle.bf16_bits_to_f64(vc)
+    ref = np.zeros((1, hq, d)), np.zeros((1, hq))
+    for h in range(hq):
+        o, l = oracle.softmax_attention(oracle.bf16_bits_to_f64(q[0, h])[None], kf[:, h],
+                                        vf[:, h], [max_len], scale_for(d))
+        ref[0][0, h], ref[1][0, h] = o[0], l[0]
+    check("over-long, odd splits", (to_host_bits(out), lse.cpu().numpy().astype(np.float64)), ref)
 
 
 def test_decode_spike_probes_at_long_context(gpu_lib):
