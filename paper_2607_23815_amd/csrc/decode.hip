@@ -260,7 +260,7 @@ hipError_t launch_decode(const KvView& kv, const uint16_t* q, int32_t hq,
                          float scale, uint16_t* out, float* lse, void* workspace,
                          hipStream_t stream) {
   const DecodePlan p = decode_plan(kv, hq, num_seqs, max_seq_len, max_blocks, workspace);
-  if (p.items > INT32_MAX) return hipErrorInvalidValue;
+  if (p.items * 64 * p.parts > kGridThreads) return hipErrorInvalidValue;
   const dim3 grid((unsigned)p.items);
   const float scale_log2 = scale * kLog2e;
   hipError_t err = launch_decode_order(p, seq_lens, num_seqs, stream);

@@ -10,7 +10,10 @@ namespace pkv {
 
 // Waves of the decode kernels that the chip holds at once (two on each of 256 x 4 SIMDs).
 constexpr int64_t kWaveSlots = 2048;
-// Work items past which a launch stays at one wave each (a grid holds 2^32 threads).
+// Threads that a launch's grid can hold.
+constexpr int64_t kGridThreads = UINT32_MAX;
+// Work items past which a launch stays at one wave each: items of eight waves would run into
+// kGridThreads at 2^23 of them, where one wave each runs into it at 2^26.
 constexpr int64_t kMaxWideItems = int64_t(1) << 20;
 
 struct DecodeCut {
@@ -50,32 +53,33 @@ inline DecodeCut decode_cut(int32_t num_seqs, int32_t hkv, int32_t max_seq_len,
   // four are better: 64 sequences of 200-1000 keys 28 us against 31). One wave per item is
   // left where the pairs alone fill the chip and a share would be a step or two (512 sequences
   // of at most 128 keys: 38 us against 48; the two meet at 600 keys).
-  int64_t target;  // waves aimed at
-  if ((groups >= kWaveSlots && max_seq_len <= 512) || groups >= kMaxWideItems) {
+  if (groups >= kWaveSlots && max_seq_len <= 512)
     p.parts = 1;
-    target = 1;
-  } else if (groups < kWaveSlots / 4 && max_seq_len >= 2048) {
+  else if (groups < kWaveSlots / 4 && max_seq_len >= 2048)
     p.parts = 8;
-    target = kWaveSlots;
-  } else {
+  else
     p.parts = 4;
-    target = kWaveSlots / 2;
+  for (;;) {
+    // Splits across workgroups cost partial results and a merge launch (about 4 us), so they
+    // are made only while the items leave the chip without enough loads in flight (waves aimed
+    // at: `target`), and of at least 1024 keys (4 sequences of 24-32k keys, 32/8 heads: 87 us,
+    // at 1.6 times fewer or 2 times more splits 92-104; one sequence of 800 keys: unsplit 11.3
+    // us with its append, two splits 12.4). At most 16384 keys, so that one long sequence does
+    // not outlast the rest.
+    const int64_t target = p.parts == 1 ? 1 : p.parts == 8 ? kWaveSlots : kWaveSlots / 2;
+    const int64_t want = std::max<int64_t>(1, target / (groups * p.parts));
+    int64_t split = std::max<int64_t>((keys + want - 1) / want, 1024);
+    split = std::max<int64_t>(std::min<int64_t>(split, 16384), base_split);
+    const int64_t unit = 32 * p.parts;
+    p.split = (int32_t)((split + unit - 1) / unit * unit);
+    // Lengths are cut to the keys above and to the table's row: then every split of a cut length
+    // starts inside the row (split sizes need not be multiples of base_split), so none is empty.
+    p.max_keys = (int32_t)std::min<int64_t>({keys, (int64_t)max_blocks * 16, INT32_MAX});
+    p.max_splits = (int32_t)(((int64_t)p.max_keys + p.split - 1) / p.split);
+    p.items = groups * p.max_splits;
+    if (p.parts == 1 || p.items < kMaxWideItems) break;
+    p.parts = 1;
   }
-  // Splits across workgroups cost partial results and a merge launch (about 4 us), so they are
-  // made only while the items leave the chip without enough loads in flight, and of at least
-  // 1024 keys (4 sequences of 24-32k keys, 32/8 heads: 87 us, at 1.6 times fewer or 2 times
-  // more splits 92-104; one sequence of 800 keys: unsplit 11.3 us with its append, two
-  // splits 12.4). At most 16384 keys, so that one long sequence does not outlast the rest.
-  const int64_t want = std::max<int64_t>(1, target / (groups * p.parts));
-  int64_t split = std::max<int64_t>((keys + want - 1) / want, 1024);
-  split = std::max<int64_t>(std::min<int64_t>(split, 16384), base_split);
-  const int64_t unit = 32 * p.parts;
-  p.split = (int32_t)((split + unit - 1) / unit * unit);
-  // Lengths are cut to the keys above and to the table's row: then every split of a cut length
-  // starts inside the row (split sizes need not be multiples of base_split), so none is empty.
-  p.max_keys = (int32_t)std::min<int64_t>({keys, (int64_t)max_blocks * 16, INT32_MAX});
-  p.max_splits = (int32_t)(((int64_t)p.max_keys + p.split - 1) / p.split);
-  p.items = groups * p.max_splits;
   return p;
 }
 

@@ -79,7 +79,17 @@ hipError_t launch_mixed(const KvView& kv, int32_t hq, float scale, const uint16_
       dp.parts == 1 ? (dp.items + kDecodePerWg - 1) / kDecodePerWg : dp.items;
   const int64_t p8 = pg.items / 8;  // a multiple of 8 by construction
   const int64_t d8 = (d_wgs + 7) / 8;
-  if (8 * (p8 + d8) > INT32_MAX) return hipErrorInvalidValue;
+  if (8 * (p8 + d8) * pre::kThreads > kGridThreads) {
+    // A workgroup per item of several shares takes more of the grid than a wave per item: what
+    // does not fit any more goes out as the two launches, whose results are the same.
+    if (dp.parts == 1) return hipErrorInvalidValue;
+    const hipError_t err =
+        launch_prefill(kv, q, hq, block_tables, max_blocks, cached_lens, cu_new_lens, num_seqs, 0,
+                       max_new_len, 0, scale, out, lse, nullptr, stream);
+    if (err != hipSuccess) return err;
+    return launch_decode(kv, dq, hq, d_block_tables, d_max_blocks, seq_lens, d_num_seqs,
+                         max_seq_len, scale, d_out, d_lse, workspace, stream);
+  }
   const dim3 grid((unsigned)(8 * (p8 + d8)));
   const float scale_log2 = scale * kLog2e;
   hipError_t err = launch_decode_order(dp, seq_lens, d_num_seqs, stream);

@@ -104,3 +104,23 @@ def test_split_size_does_not_depend_on_the_table_width(cut):
         a, b = cut(num_seqs, hkv, n), cut(num_seqs, hkv, n, 1 << 16)
         assert (a.split, a.parts) == (b.split, b.parts)
         assert _splits(a, n) == _splits(b, n)
+
+
+def test_items_fit_a_grid(cut):
+    """Wherever one wave for each split of base_split keys fits a grid of 2^32 - 1 threads, the cut
+    does: more pairs and splits than workgroups of several waves have room for go to one wave
+    each (129055 x 8 pairs of 17 splits each would be 4.5e9 threads as workgroups of four)."""
+    rnd = random.Random(2)
+    limit = 2 ** 32 - 1
+    sizes = [(129055, 8, 266240), (1 << 17, 8, 1 << 18), (63, 8, 1 << 28), (1 << 20, 1, 600)]
+    for _ in range(20000):
+        sizes.append((int(2 ** rnd.uniform(0, 24)), rnd.choice([1, 4, 8, 32]),
+                      int(2 ** rnd.uniform(0, 28))))
+    seen = set()
+    for num_seqs, hkv, n in sizes:
+        c = cut(num_seqs, hkv, n)
+        base_items = num_seqs * hkv * -(-n // c.base_split)
+        if base_items * 64 <= limit:
+            assert c.items * 64 * c.parts <= limit, (num_seqs, hkv, n, c.parts, c.items)
+            seen.add(c.parts)
+    assert seen == {1, 4, 8}

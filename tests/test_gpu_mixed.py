@@ -117,3 +117,41 @@ def test_mixed_full_size_equals_separate_calls(gpu_lib):
     mix = _run(gpu_lib, case, True, pools=(pk, pv))
     assert _same(sep, mix)
     assert np.isfinite(bf16_to_f64(mix[0])).all() and np.isfinite(bf16_to_f64(mix[2])).all()
+
+
+def test_mixed_whose_grid_is_too_large_for_one_launch(gpu_lib):
+    """A loose max_new_len gives the prefill 2^24 - 1024 workgroups (most of them end at once), and
+    3000 decode items as workgroups of four waves no longer fit the grid beside them: the call
+    goes out as the two launches, with the results of the tight call."""
+    import torch
+    lib = gpu_lib
+    say("[mixed] a grid of 2^24 - 1024 + 3000 workgroups")
+    nd, max_new, max_len = 3000, 262128 * 128, 4096
+    spec = W.WorkloadSpec("mixed_wide_grid", 233, 1, 1, 64,
+                          (W.BatchSpec("prefill", 64, W.Dist.uniform(0, 40), W.Dist.uniform(1, 5)),
+                           W.BatchSpec("decode", nd, W.Dist.uniform(0, 60), W.Dist.const(1))),
+                          ("scale", 1.25))
+    case = W.make_case(spec)
+    bp, bd = case.batches
+    pk, pv = dev_pools(case)
+    dp, dd = DevBatch(bp), DevBatch(bd)
+    scale = scale_for(case.d)
+    lens = i32(bd.prefix_lens + 1)
+    tables = torch.full((64, max_new // 16), -1, dtype=torch.int32, device="cuda")
+    tables[:, :dp.tables.shape[1]] = dp.tables
+    d_tables = torch.full((nd, max_len // 16), -1, dtype=torch.int32, device="cuda")
+    d_tables[:, :dd.tables.shape[1]] = dd.tables
+    lib.pkv_kv_append(pk, pv, dp.k_new, dp.v_new, dp.tables, dp.cached, dp.cu, dp.max_new)
+    lib.pkv_kv_append(pk, pv, dd.k_new, dd.v_new, dd.tables, dd.cached, dd.cu, 1)
+    ws = lib.alloc_workspace(lib.pkv_decode_workspace_bytes(nd, 1, 1, 64, max_len))
+    got = []
+    for t, n in ((dp.tables, dp.max_new), (tables, max_new)):
+        o = torch.full((bp.total_new, 1, 64), float("nan"), dtype=torch.bfloat16, device="cuda")
+        d = torch.full((nd, 1, 64), float("nan"), dtype=torch.bfloat16, device="cuda")
+        lib.pkv_mixed_attention(pk, pv, scale, dp.q, t, dp.cached, dp.cu, n,
+                                max(n, dp.max_total), o, dd.q, d_tables, lens, max_len, d,
+                                workspace=ws)
+        torch.cuda.synchronize()
+        got.append([to_host_bits(o), to_host_bits(d)])
+    assert _same(*got)
+    assert all(np.isfinite(bf16_to_f64(x)).all() for x in got[0])
