@@ -157,8 +157,10 @@ __global__ __launch_bounds__(kOrderThreads) void decode_order_kernel(
 }
 
 
-// KV bytes (at the host's longest length) from which a decode is ordered longest first.
+// KV bytes (at the host's longest length) from which a decode is ordered longest first: items of
+// several shares, and items of one wave.
 constexpr int64_t kOrderBytes = int64_t(512) << 20;
+constexpr int64_t kOrderBytesOneWave = int64_t(400) << 20;
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -202,14 +204,19 @@ DecodePlan decode_plan(const KvView& kv, int32_t hq, int32_t num_seqs, int32_t m
                        int32_t max_blocks, void* workspace) {
   DecodePlan p{decode_cut(num_seqs, kv.hkv, max_seq_len, max_blocks)};
   const int64_t groups = (int64_t)num_seqs * kv.hkv;
-  // Longest first pays where not every wave is resident at once and the batch is long against
-  // the ordering launch (4.5 us): 256 sequences of 256-4096 keys 383 us against 399, 256 of
-  // 400-1200 154 against 156, but 200 of 50-300 30 against 27.
+  // Longest first pays where not every wave is resident at once, or each stands alone for its
+  // sequence's whole length, and the batch is long against the ordering launch (4.5 us): 256
+  // sequences of 256-4096 keys 383 us against 399, 256 of 400-1200 154 against 156, but 200 of
+  // 50-300 30 against 27. One wave per item, ordered against not: 2048 pairs of 1-513 keys 57.5
+  // us against 59.2, 3072 of 1-300 (the bytes of 450 MB) 53.9 against 55.7, 3200 of 64 dims and
+  // 1-300 keys (235 MB) 28.8 against 27.0.
   // Up to 64 sequences the waves find the order themselves (48 of 256-4096 keys, 64/8 heads:
   // 79.1 us against 81.2; 60 of 400-8000, 8/8 heads 176.4 against 177.6; short batches, which
   // take no order, would lose 2-3 us by it).
-  const bool longest_first = p.items * p.parts > kWaveSlots &&
-                             groups * max_seq_len * kv.head_dim * 4 >= (int64_t)kOrderBytes;
+  const int64_t bytes = groups * max_seq_len * kv.head_dim * 4;
+  const bool longest_first =
+      p.parts == 1 ? bytes >= kOrderBytesOneWave
+                   : p.items * p.parts > kWaveSlots && bytes >= kOrderBytes;
   p.by_rank = longest_first && num_seqs <= kRankSeqs;
   p.ordered = longest_first && !p.by_rank;
   p.order = static_cast<int32_t*>(workspace);

@@ -49,11 +49,17 @@ inline DecodeCut decode_cut(int32_t num_seqs, int32_t hkv, int32_t max_seq_len,
   // Shares per item. Cutting an item between the waves of one workgroup costs one LDS merge
   // and no launch, and evens out the waves' lengths, so four shares are the rule. Eight pay
   // where four would leave wave slots empty and some sequences are long enough to run on
-  // alone (48 sequences of 256-4096 keys, 64/8 heads: 84 us against 104; at 512 pairs and up
-  // four are better: 64 sequences of 200-1000 keys 28 us against 31). One wave per item is
-  // left where the pairs alone fill the chip and a share would be a step or two (512 sequences
-  // of at most 128 keys: 38 us against 48; the two meet at 600 keys).
-  if (groups >= kWaveSlots && max_seq_len <= 512)
+  // alone (48 sequences of 256-4096 keys, 64/8 heads: 84 us against 104); below 2048 keys they
+  // never do (32/8 heads, 1, 16 and 64 sequences of 800-1000 keys: 10.4 us against 9.6, 13.3
+  // against 12.6, 48.5 against 46.3; of 200-256 keys 8.4 = 8.4, 8.2 = 8.2, 16.7 against 12.9).
+  // One wave per item is left where the pairs alone fill the chip and the sequences are short:
+  // more pairs are more rounds of waves, which even out by themselves, so the line rises with
+  // them. One wave against four, of 1-n keys: 2048 pairs of 128 dims at n = 513 57.5 us against
+  // 57.6, at 700 74.8 against 73.4; 3072 at 513 83.2 against 87.6, at 1000 149.2 against 149.8,
+  // at 1499 216.0 against 213.7; 4096 at 513 104.2 against 109.4, at 1200 222.1 against 224.5;
+  // 4096 of 64 dims at 513 54.8 against 61.5, at 1000 97.6 against 98.5, at 1499 142.5 against
+  // 140.5; and beside a prefill of 8 sequences 3072 of 128 dims at 1000 196 against 207.
+  if (groups >= kWaveSlots && (int64_t)max_seq_len * 3 <= groups)
     p.parts = 1;
   else if (groups < kWaveSlots / 4 && max_seq_len >= 2048)
     p.parts = 8;

@@ -124,3 +124,15 @@ def test_items_fit_a_grid(cut):
             assert c.items * 64 * c.parts <= limit, (num_seqs, hkv, n, c.parts, c.items)
             seen.add(c.parts)
     assert seen == {1, 4, 8}
+
+
+def test_short_sequences_of_many_pairs_take_one_wave_each(cut):
+    """One wave per item where the pairs fill the chip and the longest sequence has at most a
+    third as many keys as there are pairs; four shares past that line, eight for few pairs and
+    long sequences."""
+    assert [cut(256, 8, n).parts for n in (1, 512, 513, 682, 683, 4096)] == [1, 1, 1, 1, 4, 4]
+    assert [cut(384, 8, n).parts for n in (513, 1024, 1025)] == [1, 1, 4]
+    assert [cut(512, 8, n).parts for n in (513, 1365, 1366)] == [1, 1, 4]
+    assert [cut(255, 8, n).parts for n in (16, 682)] == [4, 4]
+    assert [cut(48, 8, n).parts for n in (2047, 2048)] == [4, 8]
+    assert [cut(64, 8, n).parts for n in (2047, 2048)] == [4, 4]

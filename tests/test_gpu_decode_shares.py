@@ -22,13 +22,20 @@ CASES = [
     ("splits_over_64", 4, 1, 64, [70001, 65, 66000]),
     # 512 pairs and up: four shares, unsplit, longer than 2048 keys
     ("shares4_many", 64, 64, 64, [2100, 5, 300, 2047, 2048, 17, 64, 129]),
-    # one wave per item: many pairs of at most 512 keys
+    # one wave per item: many pairs of few keys
     ("one_wave", 64, 64, 64, [511, 510, 0, 1, 16, 31, 32, 33] + [7] * 24),
-    # the same pairs with one key more: four shares
+    # the same pairs with one key more
     ("one_wave_edge", 64, 64, 64, [512, 511, 0, 1, 16, 31, 32, 33] + [7] * 24),
     # longest first, the order found by the waves (64 sequences) and by a launch (65)
     ("ranked_64", 32, 32, 128, [600, 0, 5, 5, 17, 599] + [9 + k % 7 for k in range(58)]),
     ("ordered_65", 32, 32, 128, [600, 0, 5, 5, 17, 599] + [9 + k % 7 for k in range(59)]),
+    # 2048 pairs: one wave per item up to 682 keys, four shares past them
+    ("one_wave_682", 64, 64, 64, [681, 680, 0, 1, 16, 31, 32, 33] + [7] * 24),
+    ("shares4_683", 64, 64, 64, [682, 681, 0, 1, 16, 31, 32, 33] + [7] * 24),
+    # one wave per item, longest first by a launch (2080 pairs of 128 dims, 420 MB at 412 keys)
+    ("one_wave_ordered", 32, 32, 128, [411, 0, 5, 410] + [9 + k % 7 for k in range(61)]),
+    # ... and by the waves (32 sequences of 64 pairs each)
+    ("one_wave_ranked", 64, 64, 128, [500, 0, 5, 499] + [9 + k % 7 for k in range(28)]),
 ]
 
 
