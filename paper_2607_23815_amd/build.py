@@ -38,6 +38,13 @@ SOURCES = ["pool.cpp", "sched.cpp", "api.cpp", "kv_copy.hip", "block_copy.hip", 
            "prefill.hip", "mixed.hip", "validate.hip"]
 
 
+# compiler flags of the host and the device code
+FLAGS = ["-std=c++17", f"--offload-arch={ARCH}", "-fPIC", "-fvisibility=hidden",
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-sched-strategy=max-ilp",
+         "-Wall", "-Wno-unused-function", "-I", os.path.join(ROOT, "include")]
+
+
 def hipcc() -> str:
     for cand in (os.environ.get("HIPCC"), shutil.which("hipcc"), "/opt/rocm/bin/hipcc"):
         if cand and os.path.exists(cand):
@@ -59,13 +66,8 @@ def asan_runtime() -> str:
 def build(verbose: bool = False, sanitize: bool = False) -> str:
     out = ASAN_LIB if sanitize else LIB
     tmp = out + ".tmp"
-    cmd = [hipcc(), "-O1" if sanitize else "-O3", "-std=c++17", f"--offload-arch={ARCH}",
-           "-fPIC", "-shared",
-           "-fvisibility=hidden", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-mllvm", "-amdgpu-sched-strategy=max-ilp",
-           "-Wall", "-Wno-unused-function", "-I", os.path.join(ROOT, "include"),
-           "-o", tmp] + (SANITIZE_FLAGS if sanitize else []) + \
-        [os.path.join(CSRC, s) for s in SOURCES]
+    cmd = [hipcc(), "-O1" if sanitize else "-O3"] + FLAGS + ["-shared", "-o", tmp] + \
+        (SANITIZE_FLAGS if sanitize else []) + [os.path.join(CSRC, s) for s in SOURCES]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)

@@ -108,17 +108,13 @@ __device__ __forceinline__ void decode_range(
     const bf16x8 (&qf)[D / 32], const uint16_t* __restrict__ k_cache,
     const uint16_t* __restrict__ v_cache, const int32_t* __restrict__ table, int32_t max_blocks,
     int32_t hkv, int32_t num_blocks, const int kvh, const int k0, const int k1,
-    const float scale_log2, f32x4 (&acc)[D / 16], float& m, float& lpart) {
+    const float scale_log2, f32x4 (&acc_out)[D / 16], float& m_out, float& lpart_out) {
   constexpr int KK = D / 32;   // k-steps of the score product
   constexpr int DB = D / 16;   // 16-dim blocks of the value product
   constexpr int SLAB = D * kBlockSize;
   const int lane = threadIdx.x & 63;
   const int col = lane & 15;
   const int grp = lane >> 4;
-#pragma unroll
-  for (int db = 0; db < DB; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
-  m = -INFINITY;
-  lpart = 0.f;
 
   // The range's blocks in per-lane register tables of 64 entries: chunk c holds, in lane l,
   // the pool offset of the range's block 64 c + l, or of pool block 0 (a stand-in that is
@@ -147,6 +143,15 @@ __device__ __forceinline__ void decode_range(
                          : __builtin_amdgcn_readlane(tab_next, b - 64);
     return (size_t)e * hkv * SLAB + head_off;
   };
+
+  // Locals, copied out at the end: accumulated through the caller's references, the loop takes
+  // 248 registers of a wave instead of 192, and the fused launch spills (2 registers with four
+  // shares, 8 with eight).
+  f32x4 acc[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY;
+  float lpart = 0.f;
 
   auto compute = [&](const DecodeFrag<D>& f, int t0) {
     const int nvalid = min(32, k1 - t0);
@@ -224,6 +229,10 @@ __device__ __forceinline__ void decode_range(
     compute(fb, t0 + 32);
     if (t0 + 64 >= k1) break;
   }
+#pragma unroll
+  for (int db = 0; db < DB; ++db) acc_out[db] = acc[db];
+  m_out = m;
+  lpart_out = lpart;
 }
 
 // The query operand of kv head kvh: lane (col, grp) holds dims 32 kk + 8 grp .. +7 of query
