@@ -4,8 +4,8 @@
 // HBM rate, followed by a merge of the splits' partial results by their log-sum-exp weights.
 //
 // Work item = (sequence, kv head, split). Its keys are shared out among the waves of one
-// workgroup (or one wave takes them all: see decode_plan for when), each wave streams its
-// share on its own, without barriers, and the shares' results meet in LDS once at the end. Cutting
+// workgroup (or one wave takes them all: see decode_cut and kLoneKeys for when), each wave streams
+// its share on its own, without barriers, and the shares' results meet in LDS at the end. Cutting
 // inside the workgroup needs no partial results in memory and no merge launch, so splits
 // across workgroups are left to batches too small to fill the chip without them. HBM
 // bandwidth bounds a large batch (512 sequences of 512-2048 keys: 5.9 TB/s), the chain of
@@ -287,21 +287,19 @@ __device__ __forceinline__ bool decode_item(const DecodeWork& w, int32_t hkv, in
   return true;
 }
 
-// The body of a one-wave work item.
+// A work item on one wave.
 template <int D>
-__device__ __forceinline__ void decode_body(
+__device__ __forceinline__ void decode_one_wave(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache,
     const uint16_t* __restrict__ v_cache, const int32_t* __restrict__ block_tables,
     int32_t max_blocks, const DecodeWork& work, int32_t hq, int32_t hkv, int32_t num_blocks,
     float scale_log2, float* __restrict__ ws_o, float* __restrict__ ws_ml,
-    uint16_t* __restrict__ out, float* __restrict__ lse, const int64_t item) {
+    uint16_t* __restrict__ out, float* __restrict__ lse, const DecodeItem& it) {
   constexpr int DB = D / 16;
   const int g = hq / hkv;
   const int lane = threadIdx.x & 63;
   const int col = lane & 15;   // query head within the kv group (column)
   const int grp = lane >> 4;   // lane group 0..3
-  DecodeItem it;
-  if (!decode_item(work, hkv, item, it)) return;
   const int i = it.i;
   const int h = it.kvh * g + col;
   bf16x8 qf[D / 32];
@@ -337,6 +335,29 @@ __device__ __forceinline__ void decode_body(
   }
 }
 
+// The body of a one-wave work item.
+template <int D>
+__device__ __forceinline__ void decode_body(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache,
+    const uint16_t* __restrict__ v_cache, const int32_t* __restrict__ block_tables,
+    int32_t max_blocks, const DecodeWork& work, int32_t hq, int32_t hkv, int32_t num_blocks,
+    float scale_log2, float* __restrict__ ws_o, float* __restrict__ ws_ml,
+    uint16_t* __restrict__ out, float* __restrict__ lse, const int64_t item) {
+  DecodeItem it;
+  if (!decode_item(work, hkv, item, it)) return;
+  decode_one_wave<D>(q, k_cache, v_cache, block_tables, max_blocks, work, hq, hkv, num_blocks,
+                     scale_log2, ws_o, ws_ml, out, lse, it);
+}
+
+// Keys up to which one wave of a workgroup takes an item alone: with four or eight shares of a
+// step or two, the merge and the waves' slots cost more than they save. The host cannot plan for
+// it, as it knows the longest length (or a bound above it) only. 256 sequences of 10-100 keys
+// under a bound of 4096, 32/8 heads: 23.4 us as four shares, 20.7, 18.2 and 17.8 alone up to 64,
+// 96 and 128 keys, 17.3 in a launch of one wave per item; 100 of 60-120, 16/16 heads of 64 dims:
+// 14.5, 14.1, 13.0 and 10.6; 4 of 60-120 8.2 each way; 128 of 100-500 under 4096 34.6, 34.6, 34.6
+// and 35.1.
+constexpr int kLoneKeys = 128;
+
 // Shares' results of one work item on their way to each other.
 template <int D, int kParts>
 struct DecodeSmem {
@@ -363,6 +384,12 @@ __device__ __forceinline__ void decode_group_body(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   DecodeItem it;
   if (!decode_item(work, hkv, item, it)) return;  // (workgroup-uniform)
+  if (it.k1 - it.k0 <= kLoneKeys) {               // (workgroup-uniform)
+    if (wave == 0)
+      decode_one_wave<D>(q, k_cache, v_cache, block_tables, max_blocks, work, hq, hkv,
+                         num_blocks, scale_log2, ws_o, ws_ml, out, lse, it);
+    return;
+  }
   const int share = ((it.k1 - it.k0 + kParts - 1) / kParts + 31) / 32 * 32;
   bf16x8 qf[D / 32];
   decode_load_q<D>(q, it.i, hq, g, it.kvh, qf);
