@@ -2,6 +2,8 @@
 // contiguous span of hkv * D * 16 elements of the K cache ([block][hkv][D/8][16][8]), and
 // likewise its V region ([block][hkv][D][16]), so a copy is a plain 16-byte vector copy,
 // coalesced across the workgroup.
+#include <algorithm>
+
 #include "device_utils.h"
 #include "launch.h"
 
@@ -18,6 +20,7 @@ namespace {
 // within 1%, eight are slower (34.6).
 constexpr int kUnroll = 2;
 constexpr int kCopyThreads = 256;
+constexpr int64_t kMaxParts = 65535;  // (a grid's z)
 __global__ __launch_bounds__(kCopyThreads) void copy_blocks_kernel(
     uint16_t* __restrict__ k_cache, uint16_t* __restrict__ v_cache,
     const int32_t* __restrict__ pairs, int32_t num_blocks, int64_t span) {
@@ -28,14 +31,17 @@ __global__ __launch_bounds__(kCopyThreads) void copy_blocks_kernel(
   const u32x4* from = reinterpret_cast<const u32x4*>(base + (size_t)src * span);
   u32x4* to = reinterpret_cast<u32x4*>(base + (size_t)dst * span);
   const int64_t n = span / 8;  // 16-byte chunks
-  const int64_t c0 = (int64_t)blockIdx.z * (kUnroll * kCopyThreads) + threadIdx.x;
-  u32x4 v[kUnroll];
+  constexpr int64_t kPart = kUnroll * kCopyThreads;
+  // (one part each; more where the grid has not a workgroup for every part)
+  for (int64_t c0 = blockIdx.z * kPart + threadIdx.x; c0 < n; c0 += gridDim.z * kPart) {
+    u32x4 v[kUnroll];
 #pragma unroll
-  for (int k = 0; k < kUnroll; ++k)
-    if (c0 + k * kCopyThreads < n) v[k] = from[c0 + k * kCopyThreads];
+    for (int k = 0; k < kUnroll; ++k)
+      if (c0 + k * kCopyThreads < n) v[k] = from[c0 + k * kCopyThreads];
 #pragma unroll
-  for (int k = 0; k < kUnroll; ++k)
-    if (c0 + k * kCopyThreads < n) to[c0 + k * kCopyThreads] = v[k];
+    for (int k = 0; k < kUnroll; ++k)
+      if (c0 + k * kCopyThreads < n) to[c0 + k * kCopyThreads] = v[k];
+  }
 }
 
 }  // namespace
@@ -44,7 +50,8 @@ hipError_t launch_copy_blocks(const KvView& kv, const int32_t* pairs, int32_t nu
                               hipStream_t stream) {
   const int64_t span = (int64_t)kv.hkv * kv.head_dim * kBlockSize;
   const int64_t part = (int64_t)kUnroll * kCopyThreads * 8;  // elements
-  const dim3 grid((unsigned)num_pairs, 2, (unsigned)((span + part - 1) / part));
+  const dim3 grid((unsigned)num_pairs, 2,
+                  (unsigned)std::min((span + part - 1) / part, kMaxParts));
   hipLaunchKernelGGL(copy_blocks_kernel, grid, dim3(kCopyThreads), 0, stream, kv.k, kv.v, pairs,
                      kv.num_blocks, span);
   return hipGetLastError();

@@ -45,6 +45,26 @@ def test_copy_blocks_bit_exact(gpu_lib, hkv, d):
     assert not np.array_equal(ek, pk_h)  # the copies did change something
 
 
+def test_copy_blocks_of_more_parts_than_a_grid_has(gpu_lib):
+    """Regions of 65540 parts (131080 kv heads of 128 dims, 512 MB): the parts past the grid's
+    65535 are copied too, the last one included, and nothing else changes."""
+    import torch
+    hkv, d = 131080, 128
+    say(f"[copy_blocks] hkv={hkv} d={d}")
+    pk = torch.zeros((2, hkv, d // 8, 16, 8), dtype=torch.bfloat16, device="cuda")
+    pv = torch.zeros((2, hkv, d, 16), dtype=torch.bfloat16, device="cuda")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(77)
+    for t in (pk, pv):
+        t[1].view(torch.int16).random_(-2 ** 15, 2 ** 15 - 1, generator=gen)
+    keep = [t[1].clone() for t in (pk, pv)]
+    gpu_lib.pkv_copy_blocks(pk, pv, i32(np.asarray([[1, 0]], np.int32)))
+    torch.cuda.synchronize()
+    for t, want in zip((pk, pv), keep):
+        assert torch.equal(t[0].view(torch.int16), want.view(torch.int16))
+        assert torch.equal(t[1].view(torch.int16), want.view(torch.int16))
+
+
 def test_copy_on_write_continuations_of_a_cached_prefix(gpu_lib):
     import torch
     lib = gpu_lib
