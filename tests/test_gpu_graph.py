@@ -9,7 +9,8 @@ torch.cuda.CUDAGraph, whose capture stream is the current stream the bindings pa
   * the mixed-layer step: the suffix append, the decode-token append, then the fused mixed
     launch with a workspace allocated before the capture;
   * the suffix append and the prefill with its plan (ordering, key-split and merge kernels).
-Each graph is replayed three times with fresh inputs copied into its static buffers in
+The decode and the prefill plan run on both sides of the line past which a kernel of its own
+writes the longest-first order (64 sequences, 16 for the prefill). Each graph is replayed three times with fresh inputs copied into its static buffers in
 between (eager copies and a synchronisation between replays). Every replay must equal, bit for
 bit, the same calls made eagerly on a copy of the pool, pools included, and meet the oracle's
 bar."""
@@ -41,13 +42,19 @@ def _bits_equal(a, b):
                             b.view(torch.int32)))
 
 
-def test_decode_step_graph_replays(gpu_lib):
+@pytest.mark.parametrize("d,seqs,lo,hi", [
+    (128, 40, 100, 6000),   # one launch
+    (64, 80, 50, 3400),     # the ordering launch, then the decode
+])
+def test_decode_step_graph_replays(gpu_lib, d, seqs, lo, hi):
     import torch
     lib = gpu_lib
-    spec = W.WorkloadSpec("graph_decode", 240, 32, 8, 128,
-                          (W.BatchSpec("decode", 40, W.Dist.uniform(100, 6000),
+    spec = W.WorkloadSpec("graph_decode", 240, 32, 8, d,
+                          (W.BatchSpec("decode", seqs, W.Dist.uniform(lo, hi),
                                        W.Dist.const(1)),), ("scale", 1.25))
     case = W.make_case(spec)
+    if seqs > 64:  # the keys that call for an order (512 MB at the longest length)
+        assert seqs * 8 * (int(case.batches[0].prefix_lens.max()) + 1) * d * 4 >= 512 << 20
     b = case.batches[0]
     say(f"[graph] decode step: {b.n_seqs} sequences, contexts up to {int(b.prefix_lens.max())}")
     pk, pv = dev_pools(case)
@@ -172,14 +179,19 @@ def test_mixed_step_graph_replays(gpu_lib):
                     dl, atol_max=LSE_MAX, atol_mean=LSE_MEAN)
 
 
-def test_prefill_plan_graph_replays(gpu_lib):
-    """The prefill with its plan (key split and merge, longest-first order; three launches)
-    after the suffix append, captured and replayed."""
+@pytest.mark.parametrize("prefixes,news", [
+    ([9000, 5100, 2600], [37, 150, 90]),                             # ranked in the launch
+    ([9000, 5100, 2600] + [100 + 37 * k for k in range(17)],         # 20 sequences: the ordering
+     [17, 30, 9] + [1 + k for k in range(17)]),                      # launch
+], ids=["ranked", "ordered"])
+def test_prefill_plan_graph_replays(gpu_lib, prefixes, news):
+    """The prefill with its plan (longest-first order, key split and merge; two launches up to 16
+    sequences, three past them) after the suffix append, captured and replayed."""
     import torch
     from tests.test_gpu_prefill import _edge_spec
     lib = gpu_lib
-    spec = _edge_spec("graph_plan", 241, 32, 8, 128, 3)
-    case = W.make_case(spec, prefix_override=[[9000, 5100, 2600]], new_override=[[37, 150, 90]])
+    spec = _edge_spec("graph_plan", 241, 32, 8, 128, len(prefixes))
+    case = W.make_case(spec, prefix_override=[prefixes], new_override=[news])
     b = case.batches[0]
     pk, pv = dev_pools(case)
     pk_e, pv_e = pk.clone(), pv.clone()

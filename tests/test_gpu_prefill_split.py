@@ -148,13 +148,17 @@ def test_split_long_prefix_few_tuples_full_size(gpu_lib):
     check("long_prefix_few_tuples", case, (out, lse), oracle_prefill(case))
 
 
-def test_ordered_prefill_is_bit_identical(gpu_lib):
-    """With a workspace, a batch whose keys reach 8192 takes its sequences longest first (2048
-    work items here, so no split): the order moves work items, not arithmetic, so the output is
-    bit-identical to the launch without a workspace, and meets the bar against the oracle."""
-    say("[prefill plan] longest-first order")
+@pytest.mark.parametrize("more", [0, 1, 24])
+def test_ordered_prefill_is_bit_identical(gpu_lib, more):
+    """With a workspace, a batch whose keys reach 8192 takes its sequences longest first (2048 work
+    items or more here, so no split): the order moves work items, not arithmetic, so the output is
+    bit-identical to the launch without a workspace, and meets the bar against the oracle. Up to
+    16 sequences every wave ranks them, past 16 a launch writes the order."""
+    say(f"[prefill plan] longest-first order of {16 + more} sequences")
     prefixes = [300, 9000, 40, 5000, 1200, 7000, 16, 2500, 600, 8100, 64, 3000, 90, 4000, 128, 6000]
     news = [512, 17, 300, 128, 64, 512, 1, 200, 480, 33, 256, 100, 512, 7, 150, 90]
+    prefixes += [(701 * k) % 1900 for k in range(more)]
+    news += [1 + (37 * k) % 90 for k in range(more)]
     spec = _edge_spec("order", 190, 32, 8, 128, len(prefixes))
     case = W.make_case(spec, prefix_override=[prefixes], new_override=[news])
     a = run(gpu_lib, case)
