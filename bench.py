@@ -86,9 +86,10 @@ def source_hash(*names):
 
 KERNEL_SOURCES = {
     "prefill": ("prefill.hip", "prefill_impl.h", "device_utils.h"),
-    "decode": ("decode.hip", "decode_impl.h", "device_utils.h"),
+    "decode": ("decode.hip", "decode_impl.h", "decode_cut.h", "decode_plan.h", "device_utils.h"),
     "append": ("kv_copy.hip", "device_utils.h"),
-    "mixed": ("mixed.hip", "prefill_impl.h", "decode_impl.h", "decode.hip", "device_utils.h"),
+    "mixed": ("mixed.hip", "prefill_impl.h", "decode_impl.h", "decode.hip", "decode_cut.h",
+              "decode_plan.h", "device_utils.h"),
 }
 
 

@@ -277,11 +277,11 @@ pkv_status pkv_kv_append(const pkv_paged_kv* kv, const void* k_new, const void* 
  * cut points depend on key positions and host arguments only, so results are
  * deterministic. Order (optional, the same workspace): a batch of more than one sequence
  * whose keys reach 8192 (max_total_len >= 8192) takes its sequences longest first (a small
- * kernel writes the order into the workspace; few sequences are ranked in the launch), so the launch does not end on a few long
- * items; the order moves work items, not arithmetic, so the results are bit-identical to
- * the unordered launch. With workspace NULL (or when the size is 0) the launch neither
- * splits nor orders; a non-NULL workspace smaller than the size is refused. Calls sharing a
- * workspace must not overlap. */
+ * kernel writes the order into the workspace; up to 16 sequences are ranked in the launch), so
+ * that the launch does not end on a few long items; the order moves work items, not arithmetic,
+ * so the results are bit-identical to the unordered launch. With workspace NULL (or when the
+ * size is 0) the launch neither splits nor orders; a non-NULL workspace smaller than the size
+ * is refused. Calls sharing a workspace must not overlap. */
 pkv_status pkv_prefill_attention(const pkv_paged_kv* kv, const void* q, int32_t num_q_heads,
                                  const int32_t* block_tables, int32_t max_blocks,
                                  const int32_t* cached_lens, const int32_t* cu_new_lens,
@@ -301,12 +301,12 @@ size_t pkv_prefill_workspace_bytes(int32_t num_seqs, int32_t total_new, int32_t 
  *   out[i][h] = sum_{t < seq_lens[i]} softmax_t(scale * <q[i][h], K[t]>) V[t].
  * A batch too small to fill the chip has its key ranges cut into splits; each split writes a
  * partial result to the workspace and a second kernel merges them with their log-sum-exp
- * weights. The cuts depend on the call's sizes and each sequence's length only. q, out: bf16 [num_seqs][num_q_heads][head_dim]; lse: float
- * [num_seqs][num_q_heads] or NULL; seq_lens: int32 [num_seqs], each >= 1. max_seq_len (host)
- * >= every seq_lens[i]. workspace: device memory of at least pkv_decode_workspace_bytes
- * (non-zero whenever num_seqs > 0: it also holds the order in which the sequences of a long
- * batch are scheduled, longest first), 16-byte aligned, owned by the caller, not read back; calls
- * that share a workspace must not overlap. */
+ * weights. The cuts depend on the call's sizes and each sequence's length only. q, out: bf16
+ * [num_seqs][num_q_heads][head_dim]; lse: float [num_seqs][num_q_heads] or NULL; seq_lens:
+ * int32 [num_seqs], each >= 1. max_seq_len (host) >= every seq_lens[i]. workspace: device
+ * memory of at least pkv_decode_workspace_bytes (non-zero whenever num_seqs > 0: it also holds
+ * the order in which the sequences of a long batch are scheduled, longest first), 16-byte
+ * aligned, owned by the caller, not read back; calls that share a workspace must not overlap. */
 pkv_status pkv_decode_attention(const pkv_paged_kv* kv, const void* q, int32_t num_q_heads,
                                 const int32_t* block_tables, int32_t max_blocks,
                                 const int32_t* seq_lens, int32_t num_seqs, int32_t max_seq_len,
@@ -344,12 +344,14 @@ pkv_status pkv_copy_blocks(const pkv_paged_kv* kv, const int32_t* pairs, int32_t
 /* Mixed prefill + decode (the mixed batch of a serving step: downstream operators
  * prefilling their suffixes while other tuples decode). Identical results, bit for bit, to
  * pkv_prefill_attention on the prefill arguments (q .. lse, as there, without a workspace:
- * the fused launch does not split keys) followed by pkv_decode_attention on the decode arguments (dq .. d_lse, with workspace and
- * workspace_bytes as there), with the same num_q_heads and scale; either batch may be empty
+ * the fused launch does not split keys) followed by pkv_decode_attention on the decode
+ * arguments (dq .. d_lse, with workspace and workspace_bytes as there), with the same
+ * num_q_heads and scale; either batch may be empty
  * (zero sequences or zero new tokens). Both read the same pool, so the new tokens of both
  * batches must have been appended before the call. One fused kernel runs prefill workgroups
  * (matrix-core bound) and decode workgroups (HBM bound) side by side on every compute unit,
- * between the decode's ordering and merge kernels (where it has them). The two batches' outputs must not
+ * between the decode's ordering and merge kernels (where it has them); batches whose grids do
+ * not fit one launch together go out as the two launches. The two batches' outputs must not
  * overlap. Errors are those of the two calls. */
 pkv_status pkv_mixed_attention(const pkv_paged_kv* kv, int32_t num_q_heads, float scale,
                                const void* q, const int32_t* block_tables, int32_t max_blocks,

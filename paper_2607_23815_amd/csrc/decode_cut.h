@@ -23,9 +23,10 @@ struct DecodeCut {
   int64_t items;              // (sequence, kv head, split) work items
 };
 
-// The finest cut a call may be planned with, which its workspace is sized for: 4096 keys,
-// halved while a grid of one-wave items would hold fewer than 2048 waves. A function of the
-// call's sizes only, so a given call always needs the same workspace.
+// The splits a call's workspace has room for: of 4096 keys, halved while a grid of one-wave items
+// would hold fewer than 2048 waves. A function of the call's sizes only, so a given call always
+// needs the same workspace. The cut below never makes more of them, mostly fewer; the size stays
+// what callers have laid out for, and what decides the calls the fixed scratch takes.
 inline int32_t decode_split_keys(int32_t num_seqs, int32_t hkv, int32_t max_seq_len) {
   int32_t split = 4096;
   while (split > 64) {
@@ -41,7 +42,7 @@ inline int32_t decode_split_keys(int32_t num_seqs, int32_t hkv, int32_t max_seq_
 inline DecodeCut decode_cut(int32_t num_seqs, int32_t hkv, int32_t max_seq_len,
                             int32_t max_blocks) {
   DecodeCut p;
-  // What the workspace holds: the cut below never makes more splits than decode_split_keys does.
+  // What the workspace holds.
   const int32_t base_split = decode_split_keys(num_seqs, hkv, max_seq_len);
   const int64_t keys = ((int64_t)max_seq_len + base_split - 1) / base_split * base_split;
   // (sequence, kv head) pairs: the least number of work items
@@ -69,9 +70,9 @@ inline DecodeCut decode_cut(int32_t num_seqs, int32_t hkv, int32_t max_seq_len,
     // Splits across workgroups cost partial results and a merge launch (about 4 us), so they
     // are made only while the items leave the chip without enough loads in flight (waves aimed
     // at: `target`), and of at least 1024 keys (4 sequences of 24-32k keys, 32/8 heads: 87 us,
-    // at 1.6 times fewer or 2 times more splits 92-104; one sequence of 800 keys: unsplit 11.3
-    // us with its append, two splits 12.4). At most 16384 keys, so that one long sequence does
-    // not outlast the rest.
+    // at 1.6 times fewer or 2 times more splits 92-104; one sequence of 800 keys with its
+    // append: 12.1 us of kernels unsplit, 13.5 in two splits). At most 16384 keys, so that one
+    // long sequence does not outlast the rest.
     const int64_t target = p.parts == 1 ? 1 : p.parts == 8 ? kWaveSlots : kWaveSlots / 2;
     const int64_t want = std::max<int64_t>(1, target / (groups * p.parts));
     int64_t split = std::max<int64_t>((keys + want - 1) / want, 1024);

@@ -9,10 +9,10 @@
 // inside the workgroup needs no partial results in memory and no merge launch, so splits
 // across workgroups are left to batches too small to fill the chip without them. HBM
 // bandwidth bounds a large batch (512 sequences of 512-2048 keys: 5.9 TB/s), the chain of
-// dependent loads (length, table, first K/V) and the launches a small one (one sequence of
-// 800 keys with its append: 15.8 us as ordering + 64-key splits + merge launches, 11.3 us as
-// one). A long batch is taken longest first (past 64 sequences an ordering kernel runs before the
-// launch, up to 64 every wave ranks the lengths for itself).
+// dependent loads (length, table, first K/V) and the launches a small one (one sequence of 800
+// keys with its append: 17.2 us of kernels as ordering + 64-key splits + merge launches, 12.1 us
+// as one). A long batch is taken longest first (past 64 sequences an ordering kernel runs before
+// the launch, up to 64 every wave ranks the lengths for itself).
 // A wave streams 32 keys (two 16-token blocks) at a time straight from HBM into the
 // matrix-core operands:
 //   scores  S^T[32 keys][16 cols] = K[keys][D] . Q^T[D][cols]      (v_mfma 16x16x32 bf16)

@@ -46,6 +46,12 @@ void mixed_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
   if (upto > before) {
     const int64_t wg = (int64_t)before * 8 + x;
     if constexpr (kParts == 1) {
+      // The wave index goes through readfirstlane: without it every load of the item sits in a loop
+      // over lanes, as the compiler cannot tell that a wave's lanes share it. 256 sequences of
+      // 1-500 keys beside 64 prefilling ones, 64/8 heads, 345 us with it and 353 without, 256
+      // beside 8, 8/8 heads of 64 dims, 50.2 and 52.2; where the decode is most of the launch the
+      // loops hold its waves back to the prefill's good: 384 of 1-1000 beside 8, 32/8 heads, 196
+      // and 193.
       const int64_t item =
           wg * kDecodePerWg + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
       if (item >= d_items) return;

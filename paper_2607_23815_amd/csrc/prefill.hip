@@ -150,8 +150,9 @@ hipError_t launch_prefill(const KvView& kv, const uint16_t* q, int32_t hq,
   float* ws_ml = nullptr;
   char* ws = static_cast<char*>(workspace);
   // Few sequences are ranked by each wave for itself (the order's place stays unused): 2 of
-  // 9-20k keys 113.2 us against 116.8; at 64 the ranking in every workgroup of a long launch
-  // costs more than the ordering launch (1708 us against 1686).
+  // 9-20k keys 114.8 us against 117.2 with the ordering launch, 4 of 24-32k 342 against 343; at
+  // 64 the ranking in every workgroup of a long launch costs more than the ordering launch (1708
+  // us against 1686).
   const bool by_rank = sp.order && num_seqs <= kRankSeqsPrefill;
   if (by_rank) {
     ws += order_bytes(num_seqs);

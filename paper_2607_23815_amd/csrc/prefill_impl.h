@@ -639,8 +639,8 @@ __device__ __forceinline__ void prefill_body(const uint16_t* __restrict__ q, con
                     const int32_t* __restrict__ cu_new_lens, int32_t num_seqs, int32_t hq,
                     int32_t hkv, int32_t num_blocks, int32_t qtiles, float scale_log2,
                     uint16_t* __restrict__ out, float* __restrict__ lse, const unsigned wg,
-                    PrefillSmem<D>& sm, int32_t split_keys = 0, int32_t nsplit = 1, float* __restrict__ ws_o = nullptr,
-                    float* __restrict__ ws_ml = nullptr,
+                    PrefillSmem<D>& sm, int32_t split_keys = 0, int32_t nsplit = 1,
+                    float* __restrict__ ws_o = nullptr, float* __restrict__ ws_ml = nullptr,
                     const int32_t* __restrict__ order = nullptr, const bool by_rank = false) {
   // XCD-aware mapping: workgroup id b runs on XCD b % 8 (a mixed launch passes a `wg` with
   // the same residue mod 8 as its workgroup id). The unit that must stay on one XCD
@@ -665,7 +665,8 @@ __device__ __forceinline__ void prefill_body(const uint16_t* __restrict__ q, con
   const int sp = idx % nsplit;
   if (group >= num_seqs * hkv) return;
   const int kvh = group % hkv;
-  // with an order (or by_rank, at most kRankSeqs sequences), group ranks map to sequences longest first
+  // with an order (or by_rank, at most kRankSeqs sequences), group ranks map to sequences
+  // longest first
   const int i = order != nullptr ? order[group / hkv]
                 : by_rank        ? seq_at_rank(cached_lens, cu_new_lens, num_seqs, group / hkv)
                                  : group / hkv;

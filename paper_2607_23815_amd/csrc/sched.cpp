@@ -75,7 +75,8 @@ struct StepItem {
 // host fills the next slot while earlier segments run, and waits only for a slot it takes again
 // (and, with a group hook, for every segment); output and workspace are shared, in stream
 // order. With a wait after every segment the GPU stood idle for 30-60 us of each step of about
-// 110 us (48 documents of 800-4000 tokens with 17 short predicates each: 10.6 ms against 9.5).
+// 110 us (48 documents of 800-4000 tokens with 17 short predicates each: 10.6 ms of wall time
+// against 9.4; the launches' own time is 6.9 ms either way).
 class DeviceRunner {
  public:
   ~DeviceRunner() { release(); }

@@ -10,10 +10,10 @@ torch.cuda.CUDAGraph, whose capture stream is the current stream the bindings pa
     launch with a workspace allocated before the capture;
   * the suffix append and the prefill with its plan (ordering, key-split and merge kernels).
 The decode and the prefill plan run on both sides of the line past which a kernel of its own
-writes the longest-first order (64 sequences, 16 for the prefill). Each graph is replayed three times with fresh inputs copied into its static buffers in
-between (eager copies and a synchronisation between replays). Every replay must equal, bit for
-bit, the same calls made eagerly on a copy of the pool, pools included, and meet the oracle's
-bar."""
+writes the longest-first order (64 sequences, 16 for the prefill). Each graph is replayed three
+times with fresh inputs copied into its static buffers in between (eager copies and a
+synchronisation between replays). Every replay must equal, bit for bit, the same calls made
+eagerly on a copy of the pool, pools included, and meet the oracle's bar."""
 import numpy as np
 import pytest
 
