@@ -133,17 +133,16 @@ def _oracle_first_keys(case, b, seq_lens_cut, scale):
 
 
 @pytest.mark.parametrize("hq,hkv,d,ctx,max_len,cut", [
-    # one split per sequence planned (grid of 2048 waves): the over-long row is cut to 4096
+    # room for one split per sequence (2048 pairs): the over-long row is cut to 4096
     (16, 8, 64, [4200] + [20] * 255, 4096, 4096),
-    # five 64-key splits planned: the over-long row is cut to 5 x 64 keys
+    # room for five 64-key splits: the over-long row is cut to 5 x 64 keys
     (32, 8, 128, [1000, 50, 60, 70], 300, 320),
 ])
 def test_decode_over_long_length_is_cut_to_the_planned_splits(gpu_lib, hq, hkv, d, ctx, max_len,
                                                               cut):
     """A sequence longer than the host's max_seq_len (a broken caller contract) is cut to the
-    splits the launch planned: the call stays inside its workspace (no split beyond the
-    planned ones, no partial result without a workspace slot) and attends over that many
-    keys; every other row is unaffected."""
+    splits its workspace has room for: the call stays inside its workspace (no partial result
+    without a slot) and attends over that many keys; every other row is unaffected."""
     import torch
     say(f"[decode] over-long length hq={hq} hkv={hkv} d={d} B={len(ctx)} max_seq_len={max_len}")
     spec = W.WorkloadSpec(f"decode_overlong_{hq}_{d}", 160 + d, hq, hkv, d,
