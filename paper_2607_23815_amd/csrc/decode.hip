@@ -76,17 +76,7 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(
       den += w * ws_ml[(base + s0 + lane) * 2 + 1];
     }
     const float* src = ws_o + (base + s0) * D + lane * PER;
-    // eight splits' loads at a time; past the last one its own again, taken as zeros (a zero
-    // weight would turn its infinities into NaN)
-    for (int s = 0; s < n; s += 8) {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const float ws = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), s + k));
-        const float* from = src + (size_t)min(s + k, n - 1) * D;
-#pragma unroll
-        for (int e = 0; e < PER; ++e) o[e] += ws * (s + k < n ? from[e] : 0.f);
-      }
-    }
+    for (int s = 0; s < n; s += 8) add_partials<D>(src, w, s, n, o);
   }
 #pragma unroll
   for (int k = 32; k >= 1; k >>= 1) den += __shfl_xor(den, k);

@@ -72,17 +72,7 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(
 #pragma unroll
   for (int e = 0; e < PER; ++e) acc[e] = 0.f;
   const float* src = ws_o + slot0 * D + lane * PER;
-  // eight splits' loads at a time; past the last one its own again, taken as zeros (a zero
-  // weight would turn its infinities into NaN)
-  for (int s = 0; s <= last; s += 8) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const float ws = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), s + k));
-      const float* from = src + (size_t)min(s + k, last) * D;
-#pragma unroll
-      for (int e = 0; e < PER; ++e) acc[e] += ws * (s + k <= last ? from[e] : 0.f);
-    }
-  }
+  for (int s = 0; s <= last; s += 8) add_partials<D>(src, w, s, last + 1, acc);
   uint16_t* dst = out + ((size_t)(row0 + j) * hq + h) * D + lane * PER;
   if constexpr (PER == 2) {
     *reinterpret_cast<uint32_t*>(dst) = pack_bf16x2(acc[0] * inv, acc[1] * inv);

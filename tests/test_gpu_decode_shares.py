@@ -82,3 +82,14 @@ def test_merge_keeps_an_infinite_value(gpu_lib):
     assert np.all(np.isposinf(out[i, :, dim]))
     out[i, :, dim] = 0.0
     assert np.isfinite(out).all()
+
+
+@pytest.mark.parametrize("c", [CASES[1], CASES[2], CASES[3]], ids=lambda c: c[0])
+def test_merge_ignores_what_lies_past_the_last_split(gpu_lib, monkeypatch, c):
+    """The merge takes eight splits at a time; in a group that the last split does not fill,
+    whatever stands in the workspace past its partials stays out of the result (NaN here)."""
+    say(f"[decode shares] workspace of NaN, {c[0]}")
+    case = _case(c)
+    alloc = gpu_lib.alloc_workspace
+    monkeypatch.setattr(gpu_lib, "alloc_workspace", lambda n: alloc(n).fill_(0xFF))
+    check(c[0], run_decode(gpu_lib, case), oracle_decode(case))
