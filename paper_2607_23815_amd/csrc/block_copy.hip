@@ -21,6 +21,7 @@ namespace {
 constexpr int kUnroll = 2;
 constexpr int kCopyThreads = 256;
 constexpr int64_t kMaxParts = 65535;  // (a grid's z)
+template <bool kMany>  // regions of more parts than the grid has: a workgroup copies several
 __global__ __launch_bounds__(kCopyThreads) void copy_blocks_kernel(
     uint16_t* __restrict__ k_cache, uint16_t* __restrict__ v_cache,
     const int32_t* __restrict__ pairs, int32_t num_blocks, int64_t span) {
@@ -32,8 +33,8 @@ __global__ __launch_bounds__(kCopyThreads) void copy_blocks_kernel(
   u32x4* to = reinterpret_cast<u32x4*>(base + (size_t)dst * span);
   const int64_t n = span / 8;  // 16-byte chunks
   constexpr int64_t kPart = kUnroll * kCopyThreads;
-  // (one part each; more where the grid has not a workgroup for every part)
-  for (int64_t c0 = blockIdx.z * kPart + threadIdx.x; c0 < n; c0 += gridDim.z * kPart) {
+  int64_t c0 = blockIdx.z * kPart + threadIdx.x;
+  do {
     u32x4 v[kUnroll];
 #pragma unroll
     for (int k = 0; k < kUnroll; ++k)
@@ -41,7 +42,8 @@ __global__ __launch_bounds__(kCopyThreads) void copy_blocks_kernel(
 #pragma unroll
     for (int k = 0; k < kUnroll; ++k)
       if (c0 + k * kCopyThreads < n) to[c0 + k * kCopyThreads] = v[k];
-  }
+    c0 += gridDim.z * kPart;
+  } while (kMany && c0 < n);
 }
 
 }  // namespace
@@ -50,9 +52,10 @@ hipError_t launch_copy_blocks(const KvView& kv, const int32_t* pairs, int32_t nu
                               hipStream_t stream) {
   const int64_t span = (int64_t)kv.hkv * kv.head_dim * kBlockSize;
   const int64_t part = (int64_t)kUnroll * kCopyThreads * 8;  // elements
-  const dim3 grid((unsigned)num_pairs, 2,
-                  (unsigned)std::min((span + part - 1) / part, kMaxParts));
-  hipLaunchKernelGGL(copy_blocks_kernel, grid, dim3(kCopyThreads), 0, stream, kv.k, kv.v, pairs,
+  const int64_t parts = (span + part - 1) / part;
+  const dim3 grid((unsigned)num_pairs, 2, (unsigned)std::min(parts, kMaxParts));
+  auto* kern = parts > kMaxParts ? copy_blocks_kernel<true> : copy_blocks_kernel<false>;
+  hipLaunchKernelGGL(kern, grid, dim3(kCopyThreads), 0, stream, kv.k, kv.v, pairs,
                      kv.num_blocks, span);
   return hipGetLastError();
 }
