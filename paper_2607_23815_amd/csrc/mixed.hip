@@ -5,11 +5,13 @@
 // running them one launch after the other.
 //
 // Workgroup b runs on XCD b % 8. Each XCD's list of positions b / 8 is dealt between prefill
-// and decode workgroups in proportion to their counts, spread evenly along the list; a
-// prefill workgroup keeps the XCD its index would have in a prefill-only launch (its index
+// and decode workgroups in proportion to their counts, spread evenly along the list (few and long
+// decode items go first: kFrontItems); a prefill workgroup keeps the XCD its index would have in a prefill-only launch (its index
 // has the same residue mod 8), so the (sequence, kv head) groups keep their XCD and L2. The
 // decode items follow the longest-first order of the decode launch, and the results are
 // bit-identical to a prefill launch followed by a decode launch.
+#include <algorithm>
+
 #include "decode_plan.h"
 #include "launch.h"
 #include "prefill_impl.h"
@@ -32,17 +34,17 @@ void mixed_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
                   const uint16_t* __restrict__ dq, const int32_t* __restrict__ d_tables,
                   int32_t d_max_blocks, dec::DecodeWork work, float* __restrict__ ws_o,
                   float* __restrict__ ws_ml, uint16_t* __restrict__ d_out,
-                  float* __restrict__ d_lse, int32_t p8, int32_t d8, int64_t d_items) {
+                  float* __restrict__ d_lse, int32_t spread, int32_t d8, int64_t d_items) {
   __shared__ __align__(16) union {
     pre::PrefillSmem<D> prefill;
     dec::DecodeSmem<D, kParts> decode;
   } sm;
   const unsigned x = blockIdx.x & 7;
   const unsigned pos = blockIdx.x >> 3;
-  const int64_t t8 = (int64_t)p8 + d8;
-  // decode workgroups before position pos, and up to and including it
-  const int64_t before = (int64_t)pos * d8 / t8;
-  const int64_t upto = ((int64_t)pos + 1) * d8 / t8;
+  // decode workgroups before position pos, and up to and including it: the XCD's d8 of them spread
+  // evenly over its first `spread` positions
+  const int64_t before = min((int64_t)pos * d8 / spread, (int64_t)d8);
+  const int64_t upto = min(((int64_t)pos + 1) * d8 / spread, (int64_t)d8);
   if (upto > before) {
     const int64_t wg = (int64_t)before * 8 + x;
     if constexpr (kParts == 1) {
@@ -69,6 +71,17 @@ void mixed_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k
                          lse, (unsigned)((pos - before) * 8 + x), sm.prefill);
   }
 }
+
+// Eight shares run on four waves here, two rounds each, so an item takes about twice as long as in
+// a decode launch. Where a launch has no more of them than compute units and they are long, one that
+// starts late in the list outlasts the prefill: such decode workgroups stand at the list's front. 32
+// sequences of 800-7000 keys beside 8 prefilling of 64-256 tokens, 32/8 heads: 162 us spread evenly,
+// 120 in front (131 as two launches); 32 of 256-4096 beside 2, 64/8 heads, 95 and 77. Over 420 launches
+// of 16-504 pairs, 2-64 prefilling sequences and contexts of 2-16k the front is 14% faster within this
+// line; outside it is up to 17% slower (16 of 256-4096 beside 2, 32/8 heads: 37 and 44), as the
+// prefill then has its share of every compute unit only after the decode.
+constexpr int64_t kFrontItems = 256;
+constexpr int64_t kFrontBytes = 3 << 19;  // K and V of an item: 3072 keys of 128 dims
 
 }  // namespace
 
@@ -100,6 +113,9 @@ hipError_t launch_mixed(const KvView& kv, int32_t hq, float scale, const uint16_
   const float scale_log2 = scale * kLog2e;
   hipError_t err = launch_decode_order(dp, seq_lens, d_num_seqs, stream);
   if (err != hipSuccess) return err;
+  const int64_t item_bytes = (int64_t)std::min(dp.split, max_seq_len) * kv.head_dim * 4;
+  const bool front = dp.parts == 8 && dp.items <= kFrontItems && item_bytes >= kFrontBytes;
+  const int64_t spread = front ? d8 : p8 + d8;
   const bool wide = kv.head_dim == 128;
   auto* kern = dp.parts == 1 ? (wide ? mixed_kernel<128, 1> : mixed_kernel<64, 1>)
              : dp.parts == 4 ? (wide ? mixed_kernel<128, 4> : mixed_kernel<64, 4>)
@@ -108,7 +124,7 @@ hipError_t launch_mixed(const KvView& kv, int32_t hq, float scale, const uint16_
                      max_blocks, cached_lens, cu_new_lens, num_seqs, hq, kv.hkv, kv.num_blocks,
                      (int32_t)pg.qtiles, scale_log2, out, lse, dq, d_block_tables, d_max_blocks,
                      decode_work(dp, seq_lens, d_num_seqs), dp.ws_o, dp.ws_ml, d_out, d_lse,
-                     (int32_t)p8, (int32_t)d8, dp.items);
+                     (int32_t)spread, (int32_t)d8, dp.items);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   return launch_decode_merge(kv, dp, hq, seq_lens, d_num_seqs, d_out, d_lse, stream);

@@ -36,6 +36,8 @@ CASES = [
     ("one_wave_ordered", 32, 32, 128, [411, 0, 5, 410] + [9 + k % 7 for k in range(61)]),
     # ... and by the waves (32 sequences of 64 pairs each)
     ("one_wave_ranked", 64, 64, 128, [500, 0, 5, 499] + [9 + k % 7 for k in range(28)]),
+    # eight shares, few long items (splits of 3584 keys): in the fused launch they come first
+    ("shares8_long", 32, 8, 128, [6999, 3583, 3584, 3585, 20, 0] + [50 + k for k in range(10)]),
 ]
 
 
