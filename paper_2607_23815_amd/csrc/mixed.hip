@@ -5,11 +5,12 @@
 // running them one launch after the other.
 //
 // Workgroup b runs on XCD b % 8. Each XCD's list of positions b / 8 is dealt between prefill
-// and decode workgroups in proportion to their counts, spread evenly along the list (few and long
-// decode items go first: kFrontItems); a prefill workgroup keeps the XCD its index would have in a prefill-only launch (its index
-// has the same residue mod 8), so the (sequence, kv head) groups keep their XCD and L2. The
-// decode items follow the longest-first order of the decode launch, and the results are
-// bit-identical to a prefill launch followed by a decode launch.
+// and decode workgroups in proportion to their counts, spread evenly along the list (few and
+// long decode items go first: kFrontItems); a prefill workgroup keeps the XCD its index would
+// have in a prefill-only launch (its index has the same residue mod 8), so the (sequence, kv
+// head) groups keep their XCD and L2. The decode items follow the longest-first order of the
+// decode launch, and the results are bit-identical to a prefill launch followed by a decode
+// launch.
 #include <algorithm>
 
 #include "decode_plan.h"
