@@ -10,6 +10,7 @@ namespace pkv {
 
 // Waves of the decode kernels that the chip holds at once (two on each of 256 x 4 SIMDs).
 constexpr int64_t kWaveSlots = 2048;
+constexpr int64_t kComputeUnits = 256;
 // Threads that a launch's grid can hold.
 constexpr int64_t kGridThreads = UINT32_MAX;
 // Work items past which a launch stays at one wave each: items of eight waves would run into
@@ -72,11 +73,24 @@ inline DecodeCut decode_cut(int32_t num_seqs, int32_t hkv, int32_t max_seq_len,
     // at: `target`), and of at least 1024 keys (4 sequences of 24-32k keys, 32/8 heads: 87 us,
     // at 1.6 times fewer or 2 times more splits 92-104; one sequence of 800 keys with its
     // append: 12.1 us of kernels unsplit, 13.5 in two splits). At most 16384 keys, so that one
-    // long sequence does not outlast the rest.
+    // long sequence does not outlast the rest. A workgroup of eight shares fills a compute unit:
+    // where every pair is one item and they come to a round and a bit, long sequences of nearly
+    // the same length leave most units idle in the last round. So sequences above 16384 keys are
+    // cut at 8192 there (17 of 20000-32000 keys, 8 heads of 128 dims: 448 us at 16384, 374 at
+    // 8192; 62 of 6700-21400: 703 and 612), and where pairs are few more than units those above
+    // 8192 at 4096 (33 of 15000-16000: 471 and 389). Lengths that balance by themselves pay for
+    // it (17 of 1000-32000: 223 and 241; 33 of 4000-16000: 254 and 307), though less than one wave
+    // per item did (294, 323). Up to 8192 keys they would pay more than the others gain (33 of
+    // 7000-8000: 230 unsplit, 213 at 4096; of 4000-8000 156 and 189).
     const int64_t target = p.parts == 1 ? 1 : p.parts == 8 ? kWaveSlots : kWaveSlots / 2;
     const int64_t want = std::max<int64_t>(1, target / (groups * p.parts));
     int64_t split = std::max<int64_t>((keys + want - 1) / want, 1024);
-    split = std::max<int64_t>(std::min<int64_t>(split, 16384), base_split);
+    const bool few_over = groups > kComputeUnits && groups <= kComputeUnits * 5 / 4;
+    const int64_t cap = p.parts != 8 || want > 1   ? 16384
+                        : keys > 16384             ? 8192
+                        : few_over && keys > 8192  ? 4096
+                                                   : 16384;
+    split = std::max<int64_t>(std::min<int64_t>(split, cap), base_split);
     const int64_t unit = 32 * p.parts;
     p.split = (int32_t)((split + unit - 1) / unit * unit);
     // Lengths are cut to the keys above and to the table's row: then every split of a cut length

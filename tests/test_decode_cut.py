@@ -136,3 +136,25 @@ def test_short_sequences_of_many_pairs_take_one_wave_each(cut):
     assert [cut(255, 8, n).parts for n in (16, 682)] == [4, 4]
     assert [cut(48, 8, n).parts for n in (2047, 2048)] == [4, 8]
     assert [cut(64, 8, n).parts for n in (2047, 2048)] == [4, 4]
+
+
+def test_long_sequences_of_a_round_and_a_bit_are_split(cut):
+    """Eight shares, one item per pair: sequences above 16384 keys are split at 8192, those above
+    8192 at 4096 where pairs are few more than compute units; other numbers of pairs and shorter
+    sequences keep splits of up to 16384 keys."""
+    def n_splits(seqs, n):
+        c = cut(seqs, 8, n)
+        assert c.parts == 8
+        return c.max_splits, min(c.split, 16384)
+    for seqs in (17, 32, 33, 40, 41, 63):
+        assert n_splits(seqs, 16385) == (3, 8192)
+        assert n_splits(seqs, 8192)[0] == 1
+    for seqs in (33, 40):
+        assert n_splits(seqs, 8193) == (3, 4096)
+        assert n_splits(seqs, 16384) == (4, 4096)
+    for seqs in (17, 32, 41, 63):
+        assert n_splits(seqs, 16384)[0] == 1
+    # pairs few enough for two items each: half of 32000 rounded up to 2048 keys
+    assert n_splits(16, 32000) == (2, 16384)
+    c = cut(64, 8, 32000)
+    assert (c.parts, c.split) == (4, 16384)

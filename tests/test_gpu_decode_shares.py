@@ -38,6 +38,10 @@ CASES = [
     ("one_wave_ranked", 64, 64, 128, [500, 0, 5, 499] + [9 + k % 7 for k in range(28)]),
     # eight shares, few long items (splits of 3584 keys): in the fused launch they come first
     ("shares8_long", 32, 8, 128, [6999, 3583, 3584, 3585, 20, 0] + [50 + k for k in range(10)]),
+    # eight shares, 136 pairs above 16384 keys: splits of 8192, a last split of one key
+    ("shares8_8192", 8, 8, 64, [16384, 8191, 8192, 16383] + [3 * k for k in range(13)]),
+    # 264 pairs above 8192 keys: splits of 4096, a last split of one key
+    ("shares8_4096", 8, 8, 64, [8192, 4095, 4096, 8191] + [3 * k for k in range(29)]),
 ]
 
 
